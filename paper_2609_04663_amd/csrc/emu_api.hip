@@ -50,7 +50,7 @@ int g_fallback = EMU_FALLBACK_NONE;
 int g_sgemm_split = EMU_SGEMM_SPLIT_PASS;
 std::string g_err;
 
-// Workspace: [status word (offset 0), the FP64 split state slots of two
+// Workspace: [status word (offset 0), the FP64 split states of two
 //            operands (offset 128): 2 KB header][operand A planes][operand B planes].
 // Grown only when a call needs more; the status word is preserved across growth.
 struct Workspace {
@@ -59,7 +59,7 @@ struct Workspace {
 } g_ws;
 
 constexpr size_t HDR = 2048;
-static_assert(128 + 2 * F64_SLOTS * sizeof(F64SplitState) <= HDR, "workspace header");
+static_assert(128 + 2 * sizeof(F64SplitState) <= HDR, "workspace header");
 
 int fail(int code, const char *msg) {
     g_err = msg;
@@ -233,7 +233,7 @@ int check_gemm_args(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const voi
 }
 
 struct Shape {
-    int64_t KB, RpadA, RpadB;
+    int64_t KB, RpadA, RpadB, RliveA, RliveB;
     size_t bytesA, bytesB;
 };
 
@@ -243,8 +243,10 @@ Shape plan(int64_t M, int64_t N, int64_t K, int nplanes, int64_t tile_m, int64_t
            int64_t KB = 0) {
     Shape s;
     s.KB = KB > 0 ? KB : (K + KBLK - 1) / KBLK;
-    s.RpadA = round_up(M, tile_m) + ROW_SKEW_TILES * tile_m;
-    s.RpadB = round_up(N, tile_n) + ROW_SKEW_TILES * tile_n;
+    s.RliveA = round_up(M, tile_m);
+    s.RliveB = round_up(N, tile_n);
+    s.RpadA = s.RliveA + ROW_SKEW_TILES * tile_m;
+    s.RpadB = s.RliveB + ROW_SKEW_TILES * tile_n;
     s.bytesA = (size_t)nplanes * plane_elems(s.KB, s.RpadA) * 2;
     s.bytesB = (size_t)nplanes * plane_elems(s.KB, s.RpadB) * 2;
     return s;
@@ -427,8 +429,8 @@ int emu_sgemm_ex(char transa, char transb, int64_t M, int64_t N, int64_t K, floa
     // op(A) rows are A's rows ('N') or A's columns ('T': A is K x M, packed as a
     // B operand); op(B) columns likewise; both operands in one launch
     const F32SplitOperand ops[2] = {
-        {A, ta ? K : M, ta ? M : K, lda, ta ? 1 : 0, Ap, s.RpadA},
-        {B, tb ? N : K, tb ? K : N, ldb, tb ? 0 : 1, Bp, s.RpadB}};
+        {A, ta ? K : M, ta ? M : K, lda, ta ? 1 : 0, Ap, s.RpadA, s.RliveA},
+        {B, tb ? N : K, tb ? K : N, ldb, tb ? 0 : 1, Bp, s.RpadB, s.RliveB}};
     hipError_t e = launch_split_f32(ops, 2, s.KB, ws_status(), g_stream);
     if (e != hipSuccess) return hip_fail(e, "split_f32");
     prof_mark(1);
@@ -524,8 +526,10 @@ int dgemm_run(char *base, DgemmOpts o, bool ta, bool tb, int64_t M, int64_t N, i
     // both operands in one launch per phase: op(A)'s rows are A's rows ('N') or
     // A's columns ('T', packed as a B operand), op(B)'s columns likewise
     const F64SplitOperand ops[2] = {
-        {A, ar, ac, lda, ta ? 1 : 0, o.scaled ? sc.sa : nullptr, Ap, s.RpadA, st},
-        {B, br, bc, ldb, tb ? 0 : 1, o.scaled ? sc.sb : nullptr, Bp, s.RpadB, st + F64_SLOTS}};
+        {A, ar, ac, lda, ta ? 1 : 0, o.scaled ? sc.sa : nullptr, Ap, s.RpadA,
+         s.RliveA, st},
+        {B, br, bc, ldb, tb ? 0 : 1, o.scaled ? sc.sb : nullptr, Bp, s.RpadB,
+         s.RliveB, st + 1}};
     e = launch_split_f64(ops, 2, s.KB, np, g_split_mode, d, split_status, g_stream);
     if (e != hipSuccess) return hip_fail(e, "split_f64");
     prof_mark(1);
@@ -732,7 +736,7 @@ int emu_split_f32(int64_t R, int64_t Cc, const float *X, int64_t ldx, int as_b, 
     rc = ensure_workspace(s.bytesA);
     if (rc) return rc;
     uint16_t *P = ws_planes(0);
-    const F32SplitOperand op = {X, R, Cc, ldx, as_b != 0 ? 1 : 0, P, s.RpadA};
+    const F32SplitOperand op = {X, R, Cc, ldx, as_b != 0 ? 1 : 0, P, s.RpadA, s.RliveA};
     hipError_t e = launch_split_f32(&op, 1, s.KB, ws_status(), g_stream);
     if (e != hipSuccess) return hip_fail(e, "split_f32");
     e = launch_unpack(P, 3, s.KB, s.RpadA, R, Cc, as_b != 0, comps, g_stream);
@@ -760,7 +764,7 @@ int emu_split_f64(int64_t R, int64_t Cc, const double *X, int64_t ldx, int as_b,
         if (e != hipSuccess) return hip_fail(e, "scale_exponents");
     }
     const F64SplitOperand op = {X, R, Cc, ldx, as_b != 0 ? 1 : 0, scaled ? sc.sa : nullptr, P,
-                                s.RpadA, st};
+                                s.RpadA, s.RliveA, st};
     e = launch_split_f64(&op, 1, s.KB, 6, g_split_mode, 0, ws_status(), g_stream);
     if (e != hipSuccess) return hip_fail(e, "split_f64");
     if (R > 0 && Cc > 0) {

@@ -44,7 +44,7 @@ __host__ __device__ inline int swz(int64_t row) { return (int)((row >> 2) & 3); 
 // the k-block stride (Rpad x 64 B) and the plane stride are multiples of a
 // large power of two, and every copy of a tile's k-block (all planes) lands in
 // the same few L2 channels.  Two skews break that: Rpad gets ROW_SKEW_TILES
-// extra (zero) tiles, and consecutive planes are PLANE_SKEW elements further
+// extra tiles (never read by the GEMM), and consecutive planes are PLANE_SKEW elements further
 // apart than their KB x Rpad x 32 elements (a multiple of 512: planes stay
 // 1 KB aligned).
 constexpr int ROW_SKEW_TILES = 2;
@@ -66,21 +66,28 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 constexpr unsigned ST_NAN = 1u, ST_RANGE = 2u, ST_SUBNORMAL = 4u, ST_OVERFLOW = 8u, ST_INEXACT = 16u,
                    ST_FALLBACK = 32u;
 
-// Device state of the FP64 split of one operand: the operand-wide per-level
-// maxima (bit patterns of non-negative doubles, whose unsigned order is the
-// numeric order), the exponent chain v, and the first level the pass that
-// wrote it recomputed (-1 once the chain is verified).  One slot per pass:
-// slot 0 holds the level-0 maximum, slot p + 1 the state after pass p, so a
-// pass only reads a slot that an earlier launch completed.
-struct alignas(64) F64SplitState {
-    unsigned long long maxbits[6];
+// Device state of the FP64 split of one operand, in the workspace header.  The
+// exponent chain v is speculated by the split pass, confirmed level by level
+// (`seen`), and final in vfinal once the replay kernel has run.  The slots and
+// the work counters belong to the replay passes (a mis-speculated chain): slot
+// p is written by pass p = 1 .. nlev - 1, so a pass only reads a slot that is
+// complete.
+struct F64ReplaySlot {
+    unsigned long long maxbits[6];   // operand-wide maxima max|X^(r)| (bit patterns of
+                                     // non-negative doubles, whose unsigned order is the
+                                     // numeric order)
     int v[6];
-    int replay_from;
-    int nlev;
-    int mode;
-    int pad[3];
+    int replay_from;                 // first level the pass recomputed, -1: chain verified
+    int pad;
 };
-constexpr int F64_SLOTS = 7;    // nlev <= 6 passes
+struct alignas(64) F64SplitState {
+    unsigned seen;                   // bit r: some block's maximum of level r has the
+                                     // speculated exponent
+    unsigned ticket, done[6];        // replay work distribution (operand 0's are used)
+    int v[6];                        // speculated chain
+    int vfinal[6];
+    F64ReplaySlot slot[6];
+};
 
 // One operand of an FP32 split launch.
 struct F32SplitOperand {
@@ -89,6 +96,7 @@ struct F32SplitOperand {
     int as_b;                   // packed rows are X's columns (a B operand)
     uint16_t *P;                // packed planes
     int64_t Rpad;
+    int64_t Rlive;              // packed rows the GEMM reads (Rpad without the row skew)
 };
 
 // One operand of an FP64 split launch (the GEMM splits A and B in one launch
@@ -100,7 +108,8 @@ struct F64SplitOperand {
     const int *sc;              // per-packed-row weights 2^-sc (scale-aware split) or null
     uint16_t *P;                // packed planes
     int64_t Rpad;
-    F64SplitState *st;          // F64_SLOTS slots
+    int64_t Rlive;              // packed rows the GEMM reads (Rpad without the row skew)
+    F64SplitState *st;
 };
 
 constexpr int V_ZERO = (int)0x80000000;   // level whose residual is identically zero
@@ -179,7 +188,7 @@ hipError_t launch_scale_c_f64(double *C, int64_t M, int64_t N, int64_t ldc, doub
 hipError_t launch_split_f32(const F32SplitOperand *ops, int nops, int64_t KB, unsigned *status,
                             hipStream_t s);
 // The FP64 split of nops <= 2 operands with the same KB: nlev <= 6 levels
-// (planes) each, 2 + nlev launches in all.  dcheck = d > 0 (with nops = 2, A
+// (planes) each, three launches in all.  dcheck = d > 0 (with nops = 2, A
 // then B): also set ST_INEXACT when a product of S_d may leave FP32's exact
 // range.
 hipError_t launch_split_f64(const F64SplitOperand *ops, int nops, int64_t KB, int nlev, int mode,

@@ -46,9 +46,9 @@ __device__ inline ItemCoords item_coords(int64_t pair, int RG) {
 template <bool AS_B>
 __device__ __forceinline__ void split_f32_operand(const float *__restrict__ X, int64_t rows,
                                                   int64_t cols, int64_t ldx, u16 *__restrict__ P,
-                                                  int64_t KB, int64_t Rpad,
+                                                  int64_t KB, int64_t Rpad, int64_t Rlive,
                                                   unsigned *__restrict__ status, int b, int nb) {
-    const int RG = (int)(Rpad / ROWS_PER_BLOCK);
+    const int RG = (int)(Rlive / ROWS_PER_BLOCK);
     const int64_t npairs = KB * RG;
     const int64_t prow_lim = AS_B ? cols : rows;
     const int64_t k_lim = AS_B ? rows : cols;
@@ -100,24 +100,44 @@ __global__ __launch_bounds__(SPLIT_THREADS) void split_f32_kernel(F32SplitArgs a
     const int b = (int)blockIdx.x - (second ? a.blocks0 : 0);
     const int nb = second ? (int)gridDim.x - a.blocks0 : a.blocks0;
     if (op.as_b)
-        split_f32_operand<true>(op.X, op.rows, op.cols, op.ldx, op.P, a.KB, op.Rpad, a.status, b, nb);
+        split_f32_operand<true>(op.X, op.rows, op.cols, op.ldx, op.P, a.KB, op.Rpad, op.Rlive, a.status, b, nb);
     else
-        split_f32_operand<false>(op.X, op.rows, op.cols, op.ldx, op.P, a.KB, op.Rpad, a.status, b, nb);
+        split_f32_operand<false>(op.X, op.rows, op.cols, op.ldx, op.P, a.KB, op.Rpad, op.Rlive, a.status, b, nb);
 }
 
 // ---------------------------------------------------------------------------
 // FP64 split.  The operand-wide maximum of every level is a global reduction;
 // instead of six dependent passes the split speculates the exponent chain
 // v_(r+1) = v_r - step (step = 9 for the symmetric projection, 8 for the
-// literal one) and records the true maxima of the residuals it produces.  Each
-// later pass first verifies the chain against the maxima the previous pass
-// recorded, from the first unverified level on; at the first mismatch it
-// takes the recorded maximum (exact: every earlier level was computed with
-// verified exponents), re-speculates the levels after it and recomputes them.
-// Every pass fixes at least one more level, so nlev passes suffice; once the
-// chain is verified a pass only copies its state slot forward.  Every block
-// runs the (tiny) verification itself from the previous pass's slot, so no
-// separate launch is needed between passes.
+// literal one) and records the true maxima of the residuals it produces.
+// Three launches:
+//   f64_maxabs_kernel   the level-0 maximum, one partial per block;
+//   split_f64_kernel    every block reduces those partials, speculates the
+//                       chain, writes all slices, leaves its maxima of the
+//                       levels and marks the levels whose exponent it confirms;
+//   f64_replay_kernel   returns at once when every level is confirmed (the
+//                       largest residual of a level has the speculated
+//                       exponent; it can never have a larger one).  Otherwise
+//                       it reduces the recorded maxima, takes the true exponent
+//                       of the first wrong level (exact: every earlier level
+//                       was computed with verified exponents), re-speculates
+//                       the levels after it and recomputes them, pass by pass
+//                       until the chain holds; every pass fixes at least one
+//                       more level.
+// The partial maxima sit in the row skew of the planes (rows Rlive .. Rpad of
+// k-block 0, which no GEMM reads), so they cost no workspace and no atomics:
+// 4096 blocks' maxima of two levels on two cache lines took 12 of the split
+// pass's 42 us at 2048^3 (d = 3).
+
+constexpr int MAX_THREADS = 512;      // threads and blocks per operand of the maximum
+constexpr int MAX_BLOCKS = 256;
+constexpr int SPLIT_BLOCKS = 1024;    // blocks per operand of the split pass
+constexpr int REPLAY_BLOCKS = 512;    // blocks of the replay kernel, and work units
+constexpr int REPLAY_UNITS = 512;     // per operand and pass
+static_assert(REPLAY_BLOCKS <= REPLAY_UNITS, "a pass has a unit for every block");
+// the row skew of one k-block holds a partial per block (tiles have >= 64 rows)
+static_assert(ROW_SKEW_TILES * ROW_GROUP * KBLK * 2 >= SPLIT_BLOCKS * 8 && SPLIT_BLOCKS >= MAX_BLOCKS,
+              "partial maxima");
 
 __device__ inline int ceil_log2_pos(double m) {
     int e;
@@ -133,11 +153,13 @@ __device__ inline unsigned long long dbits(double x) {
 struct F64SplitArgs {
     F64SplitOperand op[2];
     int nops;
-    int blocks0;          // blocks of operand 0; the rest serve operand 1
+    int blocks0, blocks1; // blocks of operand 0; the rest serve operand 1
+    int max0, max1;       // partial level-0 maxima of the operands
     int64_t KB;
     unsigned *status;
     int dcheck;           // depth d of the product set to range-check (A = op 0,
                           // B = op 1), or 0 for none
+    int mode;             // EMU_SPLIT_*
 };
 
 // The block's operand (selected, not indexed, so that the arguments stay in the
@@ -145,133 +167,154 @@ struct F64SplitArgs {
 __device__ inline const F64SplitOperand &operand_of_block(const F64SplitArgs &a, int &b, int &nb) {
     const bool second = a.nops > 1 && (int)blockIdx.x >= a.blocks0;
     b = (int)blockIdx.x - (second ? a.blocks0 : 0);
-    nb = second ? (int)gridDim.x - a.blocks0 : a.blocks0;
+    nb = second ? a.blocks1 : a.blocks0;
     return second ? a.op[1] : a.op[0];
 }
 
-__global__ void f64_state_init(F64SplitArgs a, int nlev, int mode) {
-    const int t = threadIdx.x;
-    if (t >= a.nops * F64_SLOTS) return;
-    F64SplitState &s = a.op[t / F64_SLOTS].st[t % F64_SLOTS];
-    for (int r = 0; r < 6; ++r) { s.maxbits[r] = 0ull; s.v[r] = 0; }
-    s.replay_from = 0;
-    s.nlev = nlev;
-    s.mode = mode;
+// Partial maxima of level r: one double per block.
+__device__ inline double *partial_max(const F64SplitOperand &op, int64_t KB, int r) {
+    return reinterpret_cast<double *>(op.P + r * plane_elems(KB, op.Rpad) + op.Rlive * KBLK);
 }
 
-// max |x| over an operand (level-0 maximum, into slot 0) and the input-domain
-// checks of Eq. (bf16rangefp64).  Rows are strided over the operand's blocks,
-// columns over threads.  With weights (sc non-null) the operand is read as
+__device__ inline double wave_max(double m) {
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+    return m;
+}
+
+// max |x| over an operand (level-0 maximum) and the input-domain checks of
+// Eq. (bf16rangefp64).  A wave reads 512 consecutive entries of a row (eight
+// loads of 512 bytes in flight); a matrix without gaps between its rows is
+// read as one row.  With weights (sc non-null) the operand is read as
 // x 2^-sc[p], p the packed row of x (X's row, or X's column for a B operand),
-// and the checks apply to it.
-__global__ __launch_bounds__(SPLIT_THREADS) void f64_maxabs_kernel(F64SplitArgs a) {
-    __shared__ unsigned long long red[SPLIT_THREADS / 64];
+// and the checks apply to it.  Bound by HBM: 5.9 TB/s at 8192^2.
+__global__ __launch_bounds__(MAX_THREADS) void f64_maxabs_kernel(F64SplitArgs a) {
+    __shared__ double red[MAX_THREADS / 64];
     int b, nb;
     const F64SplitOperand &op = operand_of_block(a, b, nb);
+    if (b == 0) {   // the state of the passes that follow
+        unsigned *w = reinterpret_cast<unsigned *>(op.st);
+        for (int i = threadIdx.x; i < (int)(sizeof(F64SplitState) / 4); i += MAX_THREADS) w[i] = 0u;
+    }
     double m = 0.0;
-    unsigned flags = 0;
+    bool nonfinite = false, range = false;
     const double lo = 0x1p-126, hi = 0x1.fep127;   // (2 - 2^-7) 2^127
-    // four independent loads in flight per thread (a row is read in steps of
-    // 4 x 256 consecutive entries)
-    constexpr int U = 4;
-    for (int64_t r = b; r < op.rows; r += nb) {
+    const bool one_row = op.sc == nullptr && op.ldx == op.cols;
+    const int64_t rows = one_row ? 1 : op.rows;
+    const int64_t cols = one_row ? op.rows * op.cols : op.cols;
+    constexpr int U = 8;
+    const int64_t segs = (cols + U * 64 - 1) / (U * 64), items = rows * segs;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int64_t it = (int64_t)b * (MAX_THREADS / 64) + wave; it < items;
+         it += (int64_t)nb * (MAX_THREADS / 64)) {
+        const int64_t r = one_row ? 0 : it / segs;
+        const int64_t c0 = (it - r * segs) * (U * 64) + lane;
         const double *row = op.X + r * op.ldx;
-        for (int64_t c0 = threadIdx.x; c0 < op.cols; c0 += U * SPLIT_THREADS) {
-            double x[U];
+        double x[U];
+        if (c0 - lane + U * 64 <= cols) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = row[c0 + u * 64];
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) x[u] = c0 + u * 64 < cols ? row[c0 + u * 64] : 0.0;
+        }
+        if (op.sc) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t c = c0 + u * SPLIT_THREADS;
-                x[u] = c < op.cols ? row[c] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t c = c0 + u * SPLIT_THREADS;
-                if (op.sc && c < op.cols) x[u] = ldexp(x[u], -op.sc[op.as_b ? c : r]);
-                const double ax = fabs(x[u]);
-                if (!__builtin_isfinite(x[u])) { flags |= ST_NAN; continue; }
-                if (x[u] != 0.0 && (ax < lo || ax > hi)) flags |= ST_RANGE;
-                if (ax > m) m = ax;
+                const int64_t c = c0 + u * 64;
+                if (c < cols) x[u] = ldexp(x[u], -op.sc[op.as_b ? c : r]);
             }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const double ax = fabs(x[u]);
+            const bool fin = __builtin_isfinite(x[u]);
+            nonfinite |= !fin;
+            range |= fin && x[u] != 0.0 && (ax < lo || ax > hi);
+            m = fmax(m, fin ? ax : 0.0);
+        }
     }
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-    flags = block_or(flags);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        red[w] = dbits(m);
+    m = wave_max(m);
+    const unsigned flags = block_or((nonfinite ? ST_NAN : 0u) | (range ? ST_RANGE : 0u));
+    if (lane == 0) {
+        red[wave] = m;
         if (flags) atomicOr(a.status, flags);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long bm = red[0];
-        for (int i = 1; i < SPLIT_THREADS / 64; ++i) bm = red[i] > bm ? red[i] : bm;
-        if (bm) atomicMax(&op.st[0].maxbits[0], bm);
+        for (int i = 1; i < MAX_THREADS / 64; ++i) m = fmax(m, red[i]);
+        partial_max(op, a.KB, 0)[b] = m;
     }
 }
 
-// Pass `pass` of the six-slice split of every operand of the launch:
+// The eight entries of work item (pair, thread): packed row ic.prow, reduction
+// indices k0 .. k0 + 7; zeros outside the operand; weights applied.
+template <bool AS_B>
+__device__ __forceinline__ void load8_f64(const F64SplitOperand &op, const ItemCoords &ic,
+                                          double (&x)[8]) {
+    const int64_t prow_lim = AS_B ? op.cols : op.rows;
+    const int64_t k_lim = AS_B ? op.rows : op.cols;
+    const int64_t k0 = ic.kb * KBLK + ic.q * 8, ldx = op.ldx;
+    const double *X = op.X;
+    const double *src = X + ic.prow * ldx + k0;
+    if (!AS_B && ic.prow < prow_lim && k0 + 8 <= k_lim &&
+        (reinterpret_cast<uintptr_t>(src) & 15u) == 0) {
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            const double2 t = *reinterpret_cast<const double2 *>(src + i);
+            x[i] = t.x;
+            x[i + 1] = t.y;
+        }
+    } else {
+        // branch-free: an entry outside the operand is read from g_zero8_f64,
+        // so the eight loads are issued together
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const bool ok = ic.prow < prow_lim && k0 + i < k_lim;
+            const double *e = ok ? X + (AS_B ? (k0 + i) * ldx + ic.prow : ic.prow * ldx + k0 + i)
+                                 : g_zero8_f64;
+            x[i] = *e;
+        }
+    }
+    if (op.sc) {
+        const int wexp = ic.prow < prow_lim ? -op.sc[ic.prow] : 0;   // weight 2^-s
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = ldexp(x[i], wexp);
+    }
+}
+
+// Levels whose slices are normal BF16 values whenever the chain is right:
+// every Z is a multiple of 2^(v - 8) of magnitude <= 2^v, so for
+// -118 <= v <= 127 a nonzero Z lies in [2^-126, 2^127] and needs at most 8
+// significant bits.  There the BF16 pattern is the top half of (float) Z,
+// the residual is A - Z, and only a non-finite Z (NaN or Inf input) can
+// raise a flag.  Other levels take the general rounding and checks.
+__device__ inline bool plain_level(int v) { return v != V_ZERO && v >= -118 && v <= 127; }
+
+// One pass of the six-slice split over a work share (units b, b + nb, ...):
 //   Z = fl64(fl64(A^(r) + Sigma) - Sigma), Sigma = c 2^(v_r + 45)
 //   (c = 0.75 symmetric, 1 literal), A_r = fl_BF16(Z) (= Z in the domain),
 //   A^(r+1) = fl64(A^(r) - A_r); zero slices for a level whose residual is 0.
-// Reads slot `pass`, writes slot pass + 1: the chain it used, the first level
-// r0 it recomputed (its slices r >= r0 are rewritten) and the maxima
-// max|A^(r+1)| of the levels after r0.  nlev <= 6 levels are computed (the
-// GEMM never reads slices >= nlev, and they do not influence slices < nlev).
+// Levels r0 .. nlev - 1 are stored, and the maxima |A^(r+1)| of the levels
+// after r0 returned in mx (the GEMM never reads slices >= nlev, and they do
+// not influence slices < nlev).  General form: any chain, any first level.
 template <bool AS_B>
-__device__ __forceinline__ void split_f64_pass(const F64SplitOperand op, int64_t KB, int b, int nb,
-                               const int (&v)[6], int r0, int nlev, double cst,
-                               F64SplitState *out, unsigned *status) {
-    __shared__ unsigned long long red[6][SPLIT_THREADS / 64];
+__device__ __forceinline__ void split_f64_pass(const F64SplitOperand &op, int64_t KB, int b, int nb,
+                                               const int (&v)[6], int r0, int nlev, double cst,
+                                               double (&mx)[6], unsigned &st) {
     double sig[6];
-    // Levels whose slices are normal BF16 values whenever the chain is right:
-    // every Z is a multiple of 2^(v - 8) of magnitude <= 2^v, so for
-    // -118 <= v <= 127 a nonzero Z lies in [2^-126, 2^127] and needs at most 8
-    // significant bits.  There the BF16 pattern is the top half of (float) Z,
-    // the residual is A - Z, and only a non-finite Z (NaN or Inf input) can
-    // raise a flag.  Other levels take the general rounding and checks.
     bool plain[6];
 #pragma unroll
     for (int r = 0; r < 6; ++r) {
         sig[r] = (v[r] == V_ZERO) ? 0.0 : ldexp(cst, v[r] + 45);
-        plain[r] = v[r] != V_ZERO && v[r] >= -118 && v[r] <= 127;
+        plain[r] = plain_level(v[r]);
     }
-    double mx[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    unsigned st = 0;
-    const int RG = (int)(op.Rpad / ROWS_PER_BLOCK);
+    const int RG = (int)(op.Rlive / ROWS_PER_BLOCK);
     const int64_t npairs = KB * RG;
-    const int64_t prow_lim = AS_B ? op.cols : op.rows;
-    const int64_t k_lim = AS_B ? op.rows : op.cols;
-    const double *X = op.X;
-    const int64_t ldx = op.ldx;
     for (int64_t pair = b; pair < npairs; pair += nb) {
         const ItemCoords ic = item_coords(pair, RG);
-        const int64_t k0 = ic.kb * KBLK + ic.q * 8;
         double x[8];
-        const int wexp = (op.sc && ic.prow < prow_lim) ? -op.sc[ic.prow] : 0;   // weight 2^-s
-        const double *src = X + ic.prow * ldx + k0;
-        if (!AS_B && ic.prow < prow_lim && k0 + 8 <= k_lim &&
-            (reinterpret_cast<uintptr_t>(src) & 15u) == 0) {
-#pragma unroll
-            for (int i = 0; i < 8; i += 2) {
-                const double2 t = *reinterpret_cast<const double2 *>(src + i);
-                x[i] = t.x;
-                x[i + 1] = t.y;
-            }
-        } else {
-            // branch-free: an entry outside the operand is read from g_zero8_f64,
-            // so the eight loads are issued together
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const bool ok = ic.prow < prow_lim && k0 + i < k_lim;
-                const double *e = ok ? X + (AS_B ? (k0 + i) * ldx + ic.prow : ic.prow * ldx + k0 + i)
-                                     : g_zero8_f64;
-                x[i] = *e;
-            }
-        }
-        if (op.sc) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = ldexp(x[i], wexp);
-        }
+        load8_f64<AS_B>(op, ic, x);
         u16x8 outp[6];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -306,49 +349,145 @@ __device__ __forceinline__ void split_f64_pass(const F64SplitOperand op, int64_t
                 *reinterpret_cast<u16x8 *>(op.P + packed_index(r, ic.kb, ic.prow, ic.q, KB, op.Rpad)) =
                     outp[r];
     }
-    // operand-wide maxima of the recomputed levels
+}
+
+// The first pass over a chain whose levels are all plain: the same values,
+// with the number of levels fixed at compile time.  About six instructions
+// per entry and level, five of them FP64.
+template <int NLEV, bool AS_B>
+__device__ __forceinline__ void split_f64_plain(const F64SplitOperand &op, int64_t KB, int b, int nb,
+                                                const int (&v)[6], double cst, double (&mx)[6],
+                                                unsigned &st) {
+    double sig[NLEV];
+#pragma unroll
+    for (int r = 0; r < NLEV; ++r) sig[r] = ldexp(cst, v[r] + 45);
+    const unsigned RG = (unsigned)(op.Rlive / ROWS_PER_BLOCK);
+    const unsigned npairs = (unsigned)(KB * RG);      // at most the planes' bytes / 4096
+    const int64_t plane = plane_elems(KB, op.Rpad);
+    bool nonfinite = false;
+    for (unsigned pair = b; pair < npairs; pair += nb) {
+        ItemCoords ic;
+        const unsigned kb = pair / RG;
+        ic.kb = kb;
+        ic.prow = (int64_t)(pair - kb * RG) * ROWS_PER_BLOCK + (threadIdx.x >> 2);
+        ic.q = threadIdx.x & 3;
+        double x[8];
+        load8_f64<AS_B>(op, ic, x);
+        unsigned outp[NLEV][4];
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            double w0 = x[i], w1 = x[i + 1];
+            // a non-finite entry is non-finite in every slice
+            nonfinite |= !__builtin_isfinite(w0) || !__builtin_isfinite(w1);
+#pragma unroll
+            for (int r = 0; r < NLEV; ++r) {
+                const double z0 = (w0 + sig[r]) - sig[r], z1 = (w1 + sig[r]) - sig[r];
+                outp[r][i / 2] = __builtin_amdgcn_perm(__float_as_uint((float)z1),
+                                                       __float_as_uint((float)z0), 0x07060302u);
+                if (r + 1 < NLEV) {
+                    w0 = w0 - z0;
+                    w1 = w1 - z1;
+                    mx[r + 1] = fmax(mx[r + 1], fabs(w0));
+                    mx[r + 1] = fmax(mx[r + 1], fabs(w1));
+                }
+            }
+        }
+        u16 *dst = op.P + packed_index(0, ic.kb, ic.prow, ic.q, KB, op.Rpad);
+#pragma unroll
+        for (int r = 0; r < NLEV; ++r)
+            *reinterpret_cast<uint4 *>(dst + r * plane) =
+                make_uint4(outp[r][0], outp[r][1], outp[r][2], outp[r][3]);
+    }
+    if (nonfinite) st |= ST_OVERFLOW;
+}
+
+// Block maxima of the levels in red[r][0 .. 3] (one per wave), after a barrier.
+__device__ inline void block_level_max(const double (&mx)[6], int r0, int nlev,
+                                       double (&red)[6][SPLIT_THREADS / 64]) {
     const int w = threadIdx.x >> 6;
 #pragma unroll
     for (int r = 1; r < 6; ++r) {
-        double m = mx[r];
-        for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-        if ((threadIdx.x & 63) == 0) red[r][w] = dbits(m);
+        if (r <= r0 || r >= nlev) continue;
+        const double m = wave_max(mx[r]);
+        if ((threadIdx.x & 63) == 0) red[r][w] = m;
+    }
+    __syncthreads();
+}
+
+// The chain speculated from the level-0 maximum.
+__device__ inline void speculate_chain(double m0, int step, int (&v)[6]) {
+    const int v0 = (m0 == 0.0) ? V_ZERO : ceil_log2_pos(m0);
+#pragma unroll
+    for (int r = 0; r < 6; ++r) v[r] = (v0 == V_ZERO) ? V_ZERO : v0 - step * r;
+}
+
+template <int NLEV>
+__global__ __launch_bounds__(SPLIT_THREADS) void split_f64_kernel(F64SplitArgs a) {
+    __shared__ double red[6][SPLIT_THREADS / 64];
+    int b, nb;
+    const F64SplitOperand &op = operand_of_block(a, b, nb);
+    const int nmax = a.nops > 1 && (int)blockIdx.x >= a.blocks0 ? a.max1 : a.max0;
+    // the operand-wide maximum from the partials of f64_maxabs_kernel
+    const double *part = partial_max(op, a.KB, 0);
+    double m0 = 0.0;
+    static_assert(MAX_BLOCKS <= SPLIT_THREADS, "one partial per thread");
+    if ((int)threadIdx.x < nmax) m0 = part[threadIdx.x];
+    m0 = wave_max(m0);
+    if ((threadIdx.x & 63) == 0) red[0][threadIdx.x >> 6] = m0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SPLIT_THREADS / 64; ++i) m0 = fmax(m0, red[0][i]);
+    m0 = __longlong_as_double(((long long)__builtin_amdgcn_readfirstlane((int)(dbits(m0) >> 32)) << 32) |
+                              (unsigned)__builtin_amdgcn_readfirstlane((int)dbits(m0)));
+    int v[6];
+    speculate_chain(m0, a.mode ? 8 : 9, v);
+    if (b == 0 && threadIdx.x == 0)
+        for (int r = 0; r < 6; ++r) op.st->v[r] = v[r];
+    const double cst = a.mode ? 1.0 : 0.75;
+    double mx[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    unsigned st = 0;
+    if (plain_level(v[0]) && plain_level(v[NLEV - 1])) {   // v descends
+        if (op.as_b) split_f64_plain<NLEV, true>(op, a.KB, b, nb, v, cst, mx, st);
+        else split_f64_plain<NLEV, false>(op, a.KB, b, nb, v, cst, mx, st);
+    } else {
+        if (op.as_b) split_f64_pass<true>(op, a.KB, b, nb, v, 0, NLEV, cst, mx, st);
+        else split_f64_pass<false>(op, a.KB, b, nb, v, 0, NLEV, cst, mx, st);
     }
     st = block_or(st);
-    if ((threadIdx.x & 63) == 0 && st) atomicOr(status, st);
-    __syncthreads();
-    if (threadIdx.x < 6 && threadIdx.x >= 1) {
-        const int r = threadIdx.x;
-        if (r > r0 && r < nlev) {
-            unsigned long long bm = red[r][0];
-            for (int i = 1; i < SPLIT_THREADS / 64; ++i) bm = red[r][i] > bm ? red[r][i] : bm;
-            if (bm) atomicMax(&out->maxbits[r], bm);
-        }
+    if ((threadIdx.x & 63) == 0 && st) atomicOr(a.status, st);
+    if (NLEV == 1) return;
+    block_level_max(mx, 0, NLEV, red);
+    // lane r of wave 0 holds the block's maximum of level r
+    if (threadIdx.x >= 64) return;
+    const int r = threadIdx.x;
+    bool hit = false;
+    if (r >= 1 && r < NLEV) {
+        double m = red[r][0];
+        for (int i = 1; i < SPLIT_THREADS / 64; ++i) m = fmax(m, red[r][i]);
+        partial_max(op, a.KB, r)[b] = m;
+        int vr = v[1];
+#pragma unroll
+        for (int t = 2; t < 6; ++t) vr = r == t ? v[t] : vr;
+        hit = m > 0.0 && ceil_log2_pos(m) == vr;
+    }
+    const unsigned mask = (unsigned)__ballot(hit);
+    if (threadIdx.x == 0 && mask) {
+        // once a level is confirmed the later blocks skip the atomic
+        const unsigned old = __hip_atomic_load(&op.st->seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (mask & ~old) atomicOr(&op.st->seen, mask);
     }
 }
 
-// The exponent chain pass `pass` uses, from the slot `in` the previous pass
-// wrote (slot 0, the level-0 maximum, for pass 0); returns the first level the
-// pass recomputes, or -1 once the chain is verified.  Pass p fixes level p for
-// good, so the chain of the last pass (nlev - 1) is final for levels < nlev.
-__device__ inline int chain_of(const F64SplitState &in, int pass, int step, int (&v)[6]) {
-    const int nlev = in.nlev;
-    unsigned long long mb[6];
+// Verifies the levels after rf of chain v against the maxima mb, from the
+// first unverified level on: returns -1 when the chain holds, else the first
+// level to recompute, with v corrected there and re-speculated after it.  The
+// levels after an identically zero residual are V_ZERO (their slices are zero
+// whatever exponent was speculated).
+__device__ inline int verify_chain(const unsigned long long (&mb)[6], int rf, int nlev, int step,
+                                   int (&v)[6]) {
     int r0 = -1;
-#pragma unroll
-    for (int r = 0; r < 6; ++r) { v[r] = in.v[r]; mb[r] = in.maxbits[r]; }
-    if (pass == 0) {
-        // speculate the whole chain from the level-0 maximum
-        const double m0 = __longlong_as_double((long long)mb[0]);
-        const int v0 = (m0 == 0.0) ? V_ZERO : ceil_log2_pos(m0);
-#pragma unroll
-        for (int r = 0; r < 6; ++r) v[r] = (v0 == V_ZERO) ? V_ZERO : v0 - step * r;
-        return 0;
-    }
-    // verify the levels after the previous pass's first recomputed level
-    // (compile-time level indices keep v and mb in registers)
-    const int rf = in.replay_from;
     bool done = rf < 0;
+    // (compile-time level indices keep v and mb in registers)
 #pragma unroll
     for (int r = 1; r < 6; ++r) {
         if (done || r <= rf || r >= nlev) continue;
@@ -391,35 +530,147 @@ __device__ inline bool panel_products_in_range(const int (&vA)[6], const int (&v
     return ok;
 }
 
-__global__ __launch_bounds__(SPLIT_THREADS) void split_f64_kernel(F64SplitArgs a, int pass) {
-    int b, nb;
-    const F64SplitOperand &op = operand_of_block(a, b, nb);
-    const F64SplitState &in = op.st[pass];
-    F64SplitState *out = op.st + pass + 1;
-    const int nlev = in.nlev, step = in.mode ? 8 : 9;
-    int v[6];
-    const int r0 = chain_of(in, pass, step, v);
-    if (b == 0 && threadIdx.x == 0) {
-        // levels <= r0 keep their maxima (all of them once verified); the
-        // levels after r0 are filled by this pass's atomics
-        for (int r = 0; r < 6; ++r) {
-            out->v[r] = v[r];
-            if (r0 < 0 || r <= r0) out->maxbits[r] = in.maxbits[r];
-        }
-        out->replay_from = r0;
-        out->nlev = nlev;
-        out->mode = in.mode;
-        // the last pass holds the final chains: range-check the products
-        if (a.dcheck > 0 && pass == nlev - 1 && a.nops == 2 && blockIdx.x == 0) {
-            int vb[6];
-            (void)chain_of(a.op[1].st[pass], pass, step, vb);
-            if (!panel_products_in_range(v, vb, a.dcheck)) atomicOr(a.status, ST_INEXACT);
-        }
+// The final chains (one thread of the launch).
+__device__ inline void publish_chains(const F64SplitArgs &a, const int (&v0)[6], const int (&v1)[6]) {
+    for (int r = 0; r < 6; ++r) {
+        a.op[0].st->vfinal[r] = v0[r];
+        if (a.nops > 1) a.op[1].st->vfinal[r] = v1[r];
     }
-    if (r0 < 0) return;                                   // verified: nothing to redo
-    const double cst = in.mode ? 1.0 : 0.75;
-    if (op.as_b) split_f64_pass<true>(op, a.KB, b, nb, v, r0, nlev, cst, out, a.status);
-    else split_f64_pass<false>(op, a.KB, b, nb, v, r0, nlev, cst, out, a.status);
+    if (a.dcheck > 0 && a.nops == 2 && !panel_products_in_range(v0, v1, a.dcheck))
+        atomicOr(a.status, ST_INEXACT);
+}
+
+// The chain of operand `op` after the split pass: v corrected where a level
+// was mis-speculated, and the first level to recompute (-1: none).  Uniform
+// over the block; red is block scratch.
+__device__ inline int first_verification(const F64SplitOperand &op, int64_t KB, int nblocks,
+                                         int nlev, int step, int (&v)[6],
+                                         double (&red)[6][SPLIT_THREADS / 64]) {
+#pragma unroll
+    for (int r = 0; r < 6; ++r) v[r] = op.st->v[r];
+    const unsigned want = v[0] == V_ZERO ? 0u : ((1u << nlev) - 2u);
+    if ((op.st->seen & want) == want) return -1;
+    double mx[6];
+#pragma unroll
+    for (int r = 1; r < 6; ++r) {
+        mx[r] = 0.0;
+        if (r >= nlev) continue;
+        const double *part = partial_max(op, KB, r);
+        for (int i = threadIdx.x; i < nblocks; i += SPLIT_THREADS) mx[r] = fmax(mx[r], part[i]);
+    }
+    __syncthreads();   // red may still be read by an earlier use
+    block_level_max(mx, 0, nlev, red);
+    unsigned long long mb[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int r = 1; r < 6; ++r) {
+        if (r >= nlev) continue;
+        double m = red[r][0];
+        for (int i = 1; i < SPLIT_THREADS / 64; ++i) m = fmax(m, red[r][i]);
+        mb[r] = dbits(m);
+    }
+    return verify_chain(mb, 0, nlev, step, v);
+}
+
+// The chain operand `op` has in replay pass `pass` >= 2, from the slot the
+// previous pass completed (read past the caches: another XCD wrote it).
+__device__ inline int replay_chain(const F64SplitOperand &op, int pass, int nlev, int step,
+                                   int (&v)[6]) {
+    const F64ReplaySlot &in = op.st->slot[pass - 1];
+    unsigned long long mb[6];
+#pragma unroll
+    for (int r = 0; r < 6; ++r) {
+        v[r] = __hip_atomic_load(&in.v[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mb[r] = __hip_atomic_load(&in.maxbits[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const int rf = __hip_atomic_load(&in.replay_from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return verify_chain(mb, rf, nlev, step, v);
+}
+
+// Verification of the speculated chains and, on a mismatch, up to nlev - 1
+// replay passes over the operands.  The passes follow each other inside this
+// launch: the blocks draw units of work (pass, share) from one counter, in
+// order, and the units of a pass start once every unit of the pass before has
+// been counted as done.  A unit is only drawn by a running block, which works
+// on it before it draws another, so the units that a block waits for are
+// always finished or in work: the wait ends whatever number of blocks the
+// device runs at a time, and no co-residency is assumed.  A block leaves
+// when both chains hold; it has then drawn one unit of that pass, and a pass
+// has at least as many units as the launch has blocks, so nobody waits for a
+// unit that was not drawn.
+__global__ __launch_bounds__(SPLIT_THREADS) void f64_replay_kernel(F64SplitArgs a, int nlev) {
+    __shared__ double red[6][SPLIT_THREADS / 64];
+    __shared__ unsigned drawn;
+    const int step = a.mode ? 8 : 9;
+    int va[6], vb[6] = {V_ZERO, V_ZERO, V_ZERO, V_ZERO, V_ZERO, V_ZERO};
+    const int ra = first_verification(a.op[0], a.KB, a.blocks0, nlev, step, va, red);
+    const int rb = a.nops > 1 ? first_verification(a.op[1], a.KB, a.blocks1, nlev, step, vb, red) : -1;
+    if (ra < 0 && rb < 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) publish_chains(a, va, vb);
+        return;
+    }
+    F64SplitState *ctl = a.op[0].st;
+    const unsigned units = (unsigned)(a.nops * REPLAY_UNITS);
+    const double cst = a.mode ? 1.0 : 0.75;
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) drawn = atomicAdd(&ctl->ticket, 1u);
+        __syncthreads();
+        const int pass = 1 + (int)(drawn / units), u = (int)(drawn % units);
+        if (pass >= nlev) return;
+        int wa[6], wb[6], pa = ra, pb = rb;
+        if (pass == 1) {
+#pragma unroll
+            for (int r = 0; r < 6; ++r) { wa[r] = va[r]; wb[r] = vb[r]; }
+        } else {
+            if (threadIdx.x == 0)
+                while (__hip_atomic_load(&ctl->done[pass - 1], __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT) != units)
+                    __builtin_amdgcn_s_sleep(8);
+            __syncthreads();
+            __threadfence();
+            pa = replay_chain(a.op[0], pass, nlev, step, wa);
+            pb = -1;
+            if (a.nops > 1) pb = replay_chain(a.op[1], pass, nlev, step, wb);
+            else
+#pragma unroll
+                for (int r = 0; r < 6; ++r) wb[r] = V_ZERO;
+        }
+        // the last pass's chain is final: it has fixed a level in every pass
+        const bool holds = pa < 0 && pb < 0;
+        if (u == 0 && threadIdx.x == 0 && (holds || pass == nlev - 1)) publish_chains(a, wa, wb);
+        if (holds) return;
+        const bool second = u >= REPLAY_UNITS;
+        const F64SplitOperand &op = second ? a.op[1] : a.op[0];
+        const int b = second ? u - REPLAY_UNITS : u, r0 = second ? pb : pa;
+        int v[6];
+#pragma unroll
+        for (int r = 0; r < 6; ++r) v[r] = second ? wb[r] : wa[r];
+        F64ReplaySlot *out = &op.st->slot[pass];
+        if (b == 0 && threadIdx.x == 0) {
+            for (int r = 0; r < 6; ++r) out->v[r] = v[r];
+            out->replay_from = r0;
+        }
+        if (r0 >= 0) {
+            double mx[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            unsigned st = 0;
+            if (op.as_b) split_f64_pass<true>(op, a.KB, b, REPLAY_UNITS, v, r0, nlev, cst, mx, st);
+            else split_f64_pass<false>(op, a.KB, b, REPLAY_UNITS, v, r0, nlev, cst, mx, st);
+            st = block_or(st);
+            if ((threadIdx.x & 63) == 0 && st) atomicOr(a.status, st);
+            block_level_max(mx, r0, nlev, red);
+            const int r = threadIdx.x;
+            if (r > r0 && r >= 1 && r < nlev) {
+                double m = red[r][0];
+                for (int i = 1; i < SPLIT_THREADS / 64; ++i) m = fmax(m, red[r][i]);
+                if (m > 0.0) atomicMax(&out->maxbits[r], dbits(m));
+            }
+        }
+        // the next pass rewrites slices from other XCDs: every store of this
+        // unit is written back before the unit counts as done
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0) atomicAdd(&ctl->done[pass], 1u);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -508,9 +759,14 @@ __global__ void unpack_kernel(const u16 *__restrict__ P, int nc, int64_t KB, int
     }
 }
 
-// The verified chain: the slot written by the last pass.
+// The verified chain.
 __global__ void copy_v_kernel(const F64SplitState *st, int32_t *v) {
-    if (threadIdx.x < 6) v[threadIdx.x] = st[st[0].nlev].v[threadIdx.x];
+    if (threadIdx.x < 6) v[threadIdx.x] = st->vfinal[threadIdx.x];
+}
+
+// An operand without entries: every level is zero.
+__global__ void f64_empty_kernel(F64SplitState *st) {
+    if (threadIdx.x < 6) st->vfinal[threadIdx.x] = V_ZERO;
 }
 
 template <typename T>
@@ -522,16 +778,6 @@ __global__ void fill_zero_kernel(T *C, int64_t M, int64_t N, int64_t ldc) {
 int grid_for_pairs(int64_t npairs) {
     const int64_t cap = 8192;
     return (int)(npairs < cap ? (npairs > 0 ? npairs : 1) : cap);
-}
-
-// Blocks of an FP64 split pass: about eight work items per block, between
-// 1024 and 4096 blocks per operand (fewer blocks also mean fewer atomics on
-// the per-level maxima at the end of each block; measured at N = 2048 and
-// 8192).
-int grid_for_pairs_f64(int64_t npairs) {
-    int64_t g = npairs / 8;
-    g = g < 1024 ? 1024 : (g > 4096 ? 4096 : g);
-    return (int)(npairs < g ? (npairs > 0 ? npairs : 1) : g);
 }
 
 }  // namespace
@@ -579,35 +825,56 @@ hipError_t launch_split_f32(const F32SplitOperand *ops, int nops, int64_t KB, un
     a.nops = nops;
     a.KB = KB;
     a.status = status;
-    a.blocks0 = grid_for_pairs(KB * (ops[0].Rpad / ROWS_PER_BLOCK));
-    const int g = a.blocks0 + (nops > 1 ? grid_for_pairs(KB * (ops[1].Rpad / ROWS_PER_BLOCK)) : 0);
+    a.blocks0 = grid_for_pairs(KB * (ops[0].Rlive / ROWS_PER_BLOCK));
+    const int g = a.blocks0 + (nops > 1 ? grid_for_pairs(KB * (ops[1].Rlive / ROWS_PER_BLOCK)) : 0);
     split_f32_kernel<<<g, SPLIT_THREADS, 0, s>>>(a);
     return hipGetLastError();
 }
 
-// Full FP64 split of the operands: init, level-0 maxima, then nlev passes (the
-// first speculative; each later one verifies, and replays only on a mismatch).
+// Full FP64 split of the operands: level-0 maxima, the speculative pass over all
+// levels, and its verification (which replays only on a mismatch).
 hipError_t launch_split_f64(const F64SplitOperand *ops, int nops, int64_t KB, int nlev, int mode,
                             int dcheck, unsigned *status, hipStream_t s) {
     if (nops < 1 || nops > 2 || nlev < 1 || nlev > 6 || (dcheck > 0 && nops != 2))
         return hipErrorInvalidValue;
+    for (int o = 0; o < nops; ++o)
+        if (ops[o].Rlive % ROWS_PER_BLOCK != 0 || ops[o].Rpad - ops[o].Rlive < ROW_SKEW_TILES * ROW_GROUP)
+            return hipErrorInvalidValue;
+    if (KB == 0) {   // no planes, and nowhere to keep partial maxima
+        for (int o = 0; o < nops; ++o) f64_empty_kernel<<<1, 64, 0, s>>>(ops[o].st);
+        return hipGetLastError();
+    }
     F64SplitArgs a{};
     for (int o = 0; o < nops; ++o) a.op[o] = ops[o];
     a.nops = nops;
     a.KB = KB;
     a.status = status;
     a.dcheck = dcheck;
-    f64_state_init<<<1, 64, 0, s>>>(a, nlev, mode);
-    // at most 512 blocks per operand: each ends in one atomic on the maximum
-    auto max_blocks = [](int64_t rows) { return (int)(rows < 512 ? (rows > 0 ? rows : 1) : 512); };
-    a.blocks0 = max_blocks(ops[0].rows);
-    const int gm = a.blocks0 + (nops > 1 ? max_blocks(ops[1].rows) : 0);
-    f64_maxabs_kernel<<<gm, SPLIT_THREADS, 0, s>>>(a);
-    a.blocks0 = grid_for_pairs_f64(KB * (ops[0].Rpad / ROWS_PER_BLOCK));
-    const int g =
-        a.blocks0 + (nops > 1 ? grid_for_pairs_f64(KB * (ops[1].Rpad / ROWS_PER_BLOCK)) : 0);
-    for (int pass = 0; pass < nlev; ++pass)
-        split_f64_kernel<<<g, SPLIT_THREADS, 0, s>>>(a, pass);
+    a.mode = mode;
+    auto clamp = [](int64_t n, int hi) { return (int)(n < 1 ? 1 : n < hi ? n : hi); };
+    // one 512-entry segment of a row per wave, at most MAX_BLOCKS blocks per operand
+    auto max_blocks = [&](const F64SplitOperand &o) {
+        const int64_t segs = o.sc == nullptr && o.ldx == o.cols ? (o.rows * o.cols + 511) / 512
+                                                                : o.rows * ((o.cols + 511) / 512);
+        return clamp((segs + MAX_THREADS / 64 - 1) / (MAX_THREADS / 64), MAX_BLOCKS);
+    };
+    a.blocks0 = a.max0 = max_blocks(ops[0]);
+    a.blocks1 = a.max1 = nops > 1 ? max_blocks(ops[1]) : 0;
+    f64_maxabs_kernel<<<a.blocks0 + a.blocks1, MAX_THREADS, 0, s>>>(a);
+    // one 64-row x 32-index item per block, at most SPLIT_BLOCKS blocks per operand
+    a.blocks0 = clamp(KB * (ops[0].Rlive / ROWS_PER_BLOCK), SPLIT_BLOCKS);
+    a.blocks1 = nops > 1 ? clamp(KB * (ops[1].Rlive / ROWS_PER_BLOCK), SPLIT_BLOCKS) : 0;
+    const int g = a.blocks0 + a.blocks1;
+    switch (nlev) {
+        case 1: split_f64_kernel<1><<<g, SPLIT_THREADS, 0, s>>>(a); break;
+        case 2: split_f64_kernel<2><<<g, SPLIT_THREADS, 0, s>>>(a); break;
+        case 3: split_f64_kernel<3><<<g, SPLIT_THREADS, 0, s>>>(a); break;
+        case 4: split_f64_kernel<4><<<g, SPLIT_THREADS, 0, s>>>(a); break;
+        case 5: split_f64_kernel<5><<<g, SPLIT_THREADS, 0, s>>>(a); break;
+        default: split_f64_kernel<6><<<g, SPLIT_THREADS, 0, s>>>(a); break;
+    }
+    const int gr = g < REPLAY_BLOCKS ? g : REPLAY_BLOCKS;
+    f64_replay_kernel<<<gr, SPLIT_THREADS, 0, s>>>(a, nlev);
     return hipGetLastError();
 }
 
