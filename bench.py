@@ -55,7 +55,8 @@ _CSRC = "paper_2609_04663_amd/csrc/"
 # while their hash is unchanged)
 KERNEL_SOURCES = {
     "sgemm": [_CSRC + "gemm_f32.hip", _CSRC + "gemm_common.h", _CSRC + "emu_internal.h"],
-    "dgemm": [_CSRC + "gemm_f64.hip", _CSRC + "gemm_common.h", _CSRC + "emu_internal.h"],
+    "dgemm": [_CSRC + "gemm_f64.hip", _CSRC + "gemm_f64.h", _CSRC + "gemm_f64t.hip",
+              _CSRC + "gemm_common.h", _CSRC + "emu_internal.h"],
 }
 
 
