@@ -118,7 +118,8 @@ __global__ __launch_bounds__(256) void fallback_dgemm_kernel(
             for (int q = 0; q < 4; ++q) {
                 const int64_t m = m0 + wm * 32 + i * 16 + fk + 4 * q;
                 if (m < M && n < N)
-                    C[m * ldc + n] = out_update(acc[i][j][q], alpha, beta, Cin + m * ldcin + n);
+                    C[m * ldc + n] = out_update(acc[i][j][q], alpha, beta,
+                                                beta != 0.0 ? Cin[m * ldcin + n] : 0.0);
             }
         }
 }

@@ -126,27 +126,96 @@ __device__ inline void static_for(F &&f) {
 __device__ inline void order_fence() { __builtin_amdgcn_sched_barrier(0x6); }
 
 // Output update of the BLAS form C = alpha P + beta C, rounded as
-// fl(fl(alpha P) + fl(beta C)) with no contraction; beta == 0 never reads C
-// (BLAS convention: C may hold anything), and alpha == 1, beta == 0 stores P.
+// fl(fl(alpha P) + fl(beta C)) with no contraction; beta == 0 does not use c
+// (BLAS convention: C may hold anything and is not read), and alpha == 1, beta == 0 stores P.
 // (The operations are written here, under the pragma, rather than through
 // helper functions whose inlined bodies would still be contracted.)
-__device__ inline double out_update(double p, double alpha, double beta, const double *c) {
+__device__ inline double out_update(double p, double alpha, double beta, double c) {
 #pragma clang fp contract(off)
     const double ap = alpha * p;
     if (beta == 0.0) return ap;
-    const double bc = beta * *c;
+    const double bc = beta * c;
     return ap + bc;
 }
-__device__ inline float out_update(float p, float alpha, float beta, const float *c) {
+__device__ inline float out_update(float p, float alpha, float beta, float c) {
 #pragma clang fp contract(off)
     const float ap = alpha * p;
     if (beta == 0.0f) return ap;
-    const float bc = beta * *c;
+    const float bc = beta * c;
     return ap + bc;
 }
 
+// Stores a wave's tile, NB columns of NR values per lane: value (b, r) goes to
+// row urow(b, r) + lrow, column ucol(b) + lcol (u: uniform over the wave, l: the
+// lane's part), as C = alpha 2^(sa_row + sb_col) P + beta C (see out_update;
+// the weights only when sa is given).  full: every row and column is inside.
+// The plain store (alpha P) is a path of its own: the general one loads
+// weights and the old C of a column before its first store (a load after a store
+// waits for that store: sixteen such round trips cost the row/column scope 0.2 of
+// 3.5 ms at 16384 x 16384 x 512, d = 4), and where the two paths met again the
+// compiler waited for those loads, and so for the copies in flight, on both of
+// them (7 % of the same call without weights).  Rows and columns outside are
+// loaded from the last ones and not stored.
+template <int NB, int NR, typename T, typename V, typename R, typename Q>
+__device__ __forceinline__ void store_tile(const V &val, const R &urow, int lrow, const Q &ucol,
+                                           int lcol, bool full, int64_t M, int64_t N,
+                                           T *__restrict__ C, int64_t ldc, T alpha, T beta,
+                                           const int *__restrict__ sa,
+                                           const int *__restrict__ sb) {
+    if (sa == nullptr && beta == T(0)) {
+        const int64_t loff = lrow * ldc + lcol;
+        if (full) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    (C + urow(b, r) * ldc + ucol(b))[loff] = alpha * val(b, r);
+        } else {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                if (lcol >= N - ucol(b)) continue;
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (lrow < M - urow(b, r))
+                        (C + urow(b, r) * ldc + ucol(b))[loff] = alpha * val(b, r);
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int64_t col = ucol(b) + lcol, ccol = col < N ? col : N - 1;
+        int w[NR];
+        T old[NR];
+        if (sa != nullptr) {
+            const int col_w = sb[ccol];
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const int64_t row = urow(b, r) + lrow;
+                w[r] = sa[row < M ? row : M - 1] + col_w;
+            }
+        }
+        if (beta != T(0)) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const int64_t row = urow(b, r) + lrow;
+                old[r] = C[(row < M ? row : M - 1) * ldc + ccol];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int64_t row = urow(b, r) + lrow;
+            if (row >= M || col >= N) continue;
+            T p = val(b, r);
+            if (sa != nullptr) p = T(ldexp(p, w[r]));
+            C[row * ldc + col] = out_update(p, alpha, beta, beta != T(0) ? old[r] : T(0));
+        }
+    }
+}
+
 // Output coordinates of accumulator register r of lane l in a 32x32 block:
-// row (r / 4) * 8 + (l / 32) * 4 + r % 4, column l % 32.
-__device__ inline int acc_row(int lane, int r) { return (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3); }
+// row (r / 4) * 8 + r % 4 (acc_row) + 4 (l / 32) (acc_lrow), column l % 32.
+__device__ inline int acc_row(int r) { return (r >> 2) * 8 + (r & 3); }
+__device__ inline int acc_lrow(int lane) { return (lane >> 5) * 4; }
 
 }  // namespace emu

@@ -205,22 +205,14 @@ __global__ __launch_bounds__(256, 1) void gemm_f32_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
     // Store the wave tile.
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            const int64_t col = n0 + wn * 64 + cb * 32 + (lane & 31);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wm * 32 * RB + rb * 32 + acc_row(lane, r);
-                if (row < M && col < N) {
-                    if (part != nullptr)   // split-K: this split's sum, added by reduce_splits
-                        part[((int64_t)blockIdx.y * M + row) * N + col] = blk[rb][cb][r];
-                    else
-                        C[row * ldc + col] = out_update(blk[rb][cb][r], alpha, beta, C + row * ldc + col);
-                }
-            }
-        }
+    // split-K: this split's sum, added by reduce_splits
+    const bool whole = part == nullptr;
+    float *const dst = whole ? C : part + (int64_t)blockIdx.y * M * N;
+    store_tile<2 * RB, 16>(
+        [&](int b, int r) { return blk[b / 2][b % 2][r]; },
+        [&](int b, int r) { return m0 + (wm * RB + b / 2) * 32 + acc_row(r); }, acc_lrow(lane),
+        [&](int b) { return n0 + wn * 64 + b % 2 * 32; }, lane & 31, m0 + MT <= M && n0 + NT <= N,
+        M, N, dst, whole ? ldc : N, whole ? alpha : 1.0f, whole ? beta : 0.0f, nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -446,22 +438,14 @@ __global__ __launch_bounds__(256, 1) void gemm_f32s_kernel(
     for (int off = 32; off > 0; off >>= 1) st |= __shfl_xor(st, off);
     if (lane == 0 && st) atomicOr(status, st);
 
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-            const int64_t col = n0 + wn * 64 + cb * 32 + (lane & 31);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wm * 32 * RB + rb * 32 + acc_row(lane, r);
-                if (row < M && col < N) {
-                    if (part != nullptr)
-                        part[((int64_t)blockIdx.y * M + row) * N + col] = blk[rb][cb][r];
-                    else
-                        C[row * ldc + col] = out_update(blk[rb][cb][r], alpha, beta, C + row * ldc + col);
-                }
-            }
-        }
+    // split-K: this split's sum, added by reduce_splits
+    const bool whole = part == nullptr;
+    float *const dst = whole ? C : part + (int64_t)blockIdx.y * M * N;
+    store_tile<2 * RB, 16>(
+        [&](int b, int r) { return blk[b / 2][b % 2][r]; },
+        [&](int b, int r) { return m0 + (wm * RB + b / 2) * 32 + acc_row(r); }, acc_lrow(lane),
+        [&](int b) { return n0 + wn * 64 + b % 2 * 32; }, lane & 31, m0 + MT <= M && n0 + NT <= N,
+        M, N, dst, whole ? ldc : N, whole ? alpha : 1.0f, whole ? beta : 0.0f, nullptr, nullptr);
 }
 
 // Split-K combination: C = alpha (sum of the splits' partial sums, in split
@@ -475,7 +459,8 @@ __global__ void reduce_splits_kernel(const float *__restrict__ part, int splits,
         float p = part[i];
         for (int sp = 1; sp < splits; ++sp) p += part[sp * total + i];
         const int64_t row = i / N, col = i - row * N;
-        C[row * ldc + col] = out_update(p, alpha, beta, C + row * ldc + col);
+        C[row * ldc + col] =
+            out_update(p, alpha, beta, beta != 0.0f ? C[row * ldc + col] : 0.0f);
     }
 }
 

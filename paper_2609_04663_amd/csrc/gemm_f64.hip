@@ -27,15 +27,20 @@
 namespace emu {
 
 namespace {
-// Depths whose long reductions run on gemm_f64t_kernel (whole panels).
-constexpr bool T_DEPTH[12] = {false, false, false, true, true, true, true,
-                              false, false, false, false, false};
+int64_t padded_panels(int64_t KB) { return (KB + KB_PER_PANEL - 1) / KB_PER_PANEL * KB_PER_PANEL; }
 
 // Whether a depth-d DGEMM of an M x N output with KB k-blocks runs on
-// gemm_f64t_kernel: long reductions (K > 1024) whose (64 BM) x 64 tiles fill
-// the CUs (smaller grids keep the kernels with smaller tiles).
+// gemm_f64t_kernel: d = 3 .. 6, at least a panel, and (64 BM) x 64 tiles that
+// fill the CUs (smaller grids keep the kernels with smaller tiles).  It pads
+// the reduction to whole panels: always worth it for K > 1024, and for shorter
+// reductions while the padding costs less than the kernel gains over the
+// others on whole panels (16384 x 16384 x 512: 3 / 8 / 30 / 15 % for d = 3 .. 6;
+// 3000 x 5000 x 300, padded to 512, was 12 / 22 % slower at d = 3 / 4, 13 % faster
+// at d = 5 and 15 % slower at d = 6).
 bool use_t64(int d, int64_t M, int64_t N, int64_t KB) {
-    if (d < 3 || d > 6 || !T_DEPTH[d] || KB <= 32) return false;
+    if (d < 3 || d > 6 || KB < KB_PER_PANEL) return false;
+    constexpr int gain[7] = {0, 0, 0, 103, 107, 160, 112};   // per cent
+    if (KB <= 32 && padded_panels(KB) * 100 > KB * gain[d]) return false;
     const int64_t mt = 64 * t_bm(d);
     return ((M + mt - 1) / mt) * ((N + DGEMM_NT - 1) / DGEMM_NT) >= persistent_workgroups();
 }
@@ -47,7 +52,7 @@ int64_t dgemm_tile_rows(int d, int64_t M, int64_t N, int64_t KB) {
 }
 
 int64_t dgemm_kb_padded(int d, int64_t M, int64_t N, int64_t KB) {
-    return use_t64(d, M, N, KB) ? (KB + KB_PER_PANEL - 1) / KB_PER_PANEL * KB_PER_PANEL : KB;
+    return use_t64(d, M, N, KB) ? padded_panels(KB) : KB;
 }
 
 hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, int64_t M,

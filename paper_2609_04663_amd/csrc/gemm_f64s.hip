@@ -270,23 +270,19 @@ __global__ __launch_bounds__(256, 1) void gemm_f64_kernel(
         }
 
         // store; with the scale-aware split the row and column weights go back
-        // in here, C_mn = 2^(sa_m + sb_n) C'_mn (exact up to overflow or underflow)
-        const int col_w =
-            (sa != nullptr && n0 + wn * 32 + (lane & 31) < N) ? sb[n0 + wn * 32 + (lane & 31)] : 0;
-#pragma unroll
-        for (int b = 0; b < BM; ++b) {
-            const int64_t col = n0 + wn * 32 + (lane & 31);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wm * 32 * BM + b * 32 + acc_row(lane, r);
-                if (row < M && col < N) {
-                    double val = ACC64_LDS ? acc64_lds[((wave * BM + b) * 16 + r) * 64 + lane]
-                                           : acc64[ACC64_LDS ? 0 : b][r];
-                    if (sa != nullptr) val = ldexp(val, sa[row] + col_w);
-                    C[row * ldc + col] = out_update(val, alpha, beta, C + row * ldc + col);
-                }
-            }
-        }
+        // in here, C_mn = 2^(sa_m + sb_n) C'_mn (exact up to overflow or underflow).
+        // (The lane is laundered so that the store's addresses are not hoisted
+        // out of the tile loop into registers the k-loop needs.)
+        int sl = lane;
+        if constexpr (PERSIST) asm volatile("" : "+v"(sl));
+        store_tile<BM, 16>(
+            [&](int b, int r) {
+                return ACC64_LDS ? acc64_lds[((wave * BM + b) * 16 + r) * 64 + sl]
+                                 : acc64[ACC64_LDS ? 0 : b][r];
+            },
+            [&](int b, int r) { return m0 + (wm * BM + b) * 32 + acc_row(r); }, acc_lrow(sl),
+            [&](int) { return n0 + wn * 32; }, sl & 31, m0 + K::MT <= M && n0 + K::NT <= N, M, N, C,
+            ldc, alpha, beta, sa, sb);
     }
     // the last trips issued (unused) copies: let them land before the workgroup
     // ends and its LDS is handed to another workgroup

@@ -96,33 +96,35 @@ struct CfgT {
     static_assert(NS >= 3 && (NS - 1) * COPIES <= 63, "LDS stages");
 };
 
-template <int D, int BM, int W0, int W1>
+template <int D, int BM, int W0, int W1, bool PERSIST>
 __global__ __launch_bounds__(256, 1) void gemm_f64t_kernel(
     const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Bp, double *__restrict__ C,
     int64_t M, int64_t N, int KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
     const int *__restrict__ sa, const int *__restrict__ sb, double alpha, double beta, int nt_m,
-    int nt_n) {
+    int nt_n, int ntiles) {
     using K = CfgT<D, BM>;
     constexpr int P = K::P, NPL = K::NPL, NS = K::NS, T = K::T;
     using SC = SchedOf<D, BM, W0, W1>;
     __shared__ __attribute__((aligned(1024))) char lds[NS * K::STAGE];
 
-    // groups of 4 tile rows: the 32 tiles resident on an XCD share each A
-    // row-panel 8 ways and each B column-panel 4 ways (measured 0.7-3.4 % less
-    // GEMM time than groups of 8 at 8192^3, d = 3 .. 6)
-    int tm, tn;
-    tile_coords<4>(nt_m, nt_n, tm, tn);
+    // PERSIST: workgroup w0 of G takes tiles w0, w0 + G, ... (`mine` of them) and
+    // walks them as one sequence of k-blocks, the copies running on into the
+    // next tile; otherwise one tile per workgroup.  Groups of 4 tile rows: the
+    // 32 tiles resident on an XCD share each A row-panel 8 ways and each B
+    // column-panel 4 ways (measured 0.7-3.4 % less GEMM time than groups of 8
+    // at 8192^3, d = 3 .. 6).
+    const int G = gridDim.x;
+    const int mine = PERSIST ? (ntiles - 1 - (int)blockIdx.x) / G + 1 : 1;
     const int lane = threadIdx.x & 63;
     const unsigned lane16 = (unsigned)lane * 16u;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int64_t m0 = (int64_t)tm * K::MT, n0 = (int64_t)tn * K::NT;
 
     // Copy c of a k-block by wave w: for c < NPL BM, part 4 (c % BM) + w (16
     // rows, 1 KB) of A plane c / BM; else part w of B plane c - NPL BM.  ak, bk:
     // the copied k-block's slab of plane 0 at the tile's first row / column.
-    const char *Ag = reinterpret_cast<const char *>(Ap) + m0 * 64 + wave * 1024;
-    const char *Bg = reinterpret_cast<const char *>(Bp) + n0 * 64 + wave * 1024;
+    const char *Ag = reinterpret_cast<const char *>(Ap) + wave * 1024;
+    const char *Bg = reinterpret_cast<const char *>(Bp) + wave * 1024;
     const int64_t a_plane = plane_elems(KB, RpadA) * 2, b_plane = plane_elems(KB, RpadB) * 2;
     const int64_t a_kstep = RpadA * 64, b_kstep = RpadB * 64;
     auto issue = [&](const char *ak, const char *bk, char *dst, auto c_c) {
@@ -134,18 +136,28 @@ __global__ __launch_bounds__(256, 1) void gemm_f64t_kernel(
             copy_1k(bk + (c - NPL * BM) * b_plane,
                     dst + NPL * K::A_BYTES + (c - NPL * BM) * K::B_BYTES + wave * 1024, lane16);
     };
-    // copy cursor: the k-block whose copies are issued next (it stays on the
-    // last k-block once past it: in bounds, unused) and its stage
+    // copy cursor: the k-block whose copies are issued next and its stage; after
+    // a tile's last k-block it goes on at n_ak, n_bk, the next tile's first one
+    // (after the last tile that tile's own: in bounds, unused)
     int c_kb = 0, c_st = 0;
-    const char *c_ak = Ag, *c_bk = Bg;
+    const char *c_ak, *c_bk, *n_ak, *n_bk;
     auto cursor_next = [&]() {
-        if (c_kb + 1 < KB) {
-            ++c_kb;
-            c_ak += a_kstep;
-            c_bk += b_kstep;
-        }
+        ++c_kb;
+        const bool wrap = c_kb == KB;
+        c_kb = wrap ? 0 : c_kb;
+        c_ak = wrap ? n_ak : c_ak + a_kstep;
+        c_bk = wrap ? n_bk : c_bk + b_kstep;
         c_st = c_st + 1 == NS ? 0 : c_st + 1;
     };
+    auto tile_bases = [&](int it, const char *&ak, const char *&bk) {
+        int tm, tn;
+        tile_coords_of<4>((int)blockIdx.x + it * G, ntiles, nt_m, nt_n, tm, tn);
+        ak = Ag + (int64_t)tm * K::MT * 64;
+        bk = Bg + (int64_t)tn * K::NT * 64;
+    };
+    tile_bases(0, c_ak, c_bk);
+    n_ak = c_ak;
+    n_bk = c_bk;
     auto stage = [&](int s) -> char * { return lds + s * K::STAGE; };
 
     const int off0 = frag_offset(lane, 0), off1 = frag_offset(lane, 1);
@@ -210,12 +222,6 @@ __global__ __launch_bounds__(256, 1) void gemm_f64t_kernel(
             read_frag(0, off0, f_c, std::integral_constant<int, 0>{});
     });
 
-    double acc64[BM][16];
-#pragma unroll
-    for (int b = 0; b < BM; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc64[b][r] = 0.0;
-
     int qs = 0;   // stage of the current k-block
     // k-block kb: sub-step 0, wait + barrier, sub-step 1 with the copies of
     // k-block kb + NS (into the stage of kb, which no wave reads any more)
@@ -233,44 +239,49 @@ __global__ __launch_bounds__(256, 1) void gemm_f64t_kernel(
         cursor_next();
         qs = qn;
     };
-    // whole panels (KB is a multiple of 8: the planes are zero-padded to whole
-    // panels, which adds exact zeros to the last panel's sums); the panel's
-    // k-blocks are unrolled (a loop over them made the compiler spill the FP64
-    // tile around it)
-    for (int p0 = 0; p0 < KB; p0 += KB_PER_PANEL) {
-        kblock(std::true_type{});
+    for (int it = 0; it < mine; ++it) {
+        int tm, tn;
+        tile_coords_of<4>((int)blockIdx.x + it * G, ntiles, nt_m, nt_n, tm, tn);
+        const int64_t m0 = (int64_t)tm * K::MT, n0 = (int64_t)tn * K::NT;
+        if constexpr (PERSIST) tile_bases(it + 1 < mine ? it + 1 : it, n_ak, n_bk);
+        double acc64[BM][16];
 #pragma unroll
-        for (int kb = 1; kb < KB_PER_PANEL; ++kb) kblock(std::false_type{});
-        // panel end: widen each product exactly and add it in FP64, in order
-        // (one product at a time, so that only its values are in flight)
+        for (int b = 0; b < BM; ++b)
 #pragma unroll
-        for (int x = K::Q_VGPR * BM; x < P * BM; ++x) mfma_vacc_settle(acc[x]);
-        static_for<P>([&](auto q_c) {
-            constexpr int q = decltype(q_c)::value;
+            for (int r = 0; r < 16; ++r) acc64[b][r] = 0.0;
+        // whole panels (KB is a multiple of 8: the planes are zero-padded to
+        // whole panels, which adds exact zeros to the last panel's sums); the
+        // panel's k-blocks are unrolled (a loop over them made the compiler
+        // spill the FP64 tile around it)
+        for (int p0 = 0; p0 < KB; p0 += KB_PER_PANEL) {
+            kblock(std::true_type{});
 #pragma unroll
-            for (int b = 0; b < BM; ++b)
+            for (int kb = 1; kb < KB_PER_PANEL; ++kb) kblock(std::false_type{});
+            // panel end: widen each product exactly and add it in FP64, in order
+            // (one product at a time, so that only its values are in flight)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc64[b][r] += (double)acc[q * BM + b][r];
-            __builtin_amdgcn_sched_barrier(0);
-        });
+            for (int x = K::Q_VGPR * BM; x < P * BM; ++x) mfma_vacc_settle(acc[x]);
+            static_for<P>([&](auto q_c) {
+                constexpr int q = decltype(q_c)::value;
+#pragma unroll
+                for (int b = 0; b < BM; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc64[b][r] += (double)acc[q * BM + b][r];
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        }
+        // (the lane is laundered so that the store's addresses are not hoisted
+        // out of the tile loop into registers the k-loop needs)
+        int sl = lane;
+        if constexpr (PERSIST) asm volatile("" : "+v"(sl));
+        store_tile<BM, 16>([&](int b, int r) { return acc64[b][r]; },
+                           [&](int b, int r) { return m0 + (wm * BM + b) * 32 + acc_row(r); },
+                           acc_lrow(sl), [&](int) { return n0 + wn * 32; }, sl & 31,
+                           m0 + K::MT <= M && n0 + K::NT <= N, M, N, C, ldc, alpha, beta, sa, sb);
     }
     // the last trips issued (unused) copies: let them land before the
     // workgroup ends and its LDS is handed to another workgroup
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
-    const int64_t col = n0 + wn * 32 + (lane & 31);
-    const int col_w = (sa != nullptr && col < N) ? sb[col] : 0;
-#pragma unroll
-    for (int b = 0; b < BM; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t row = m0 + wm * 32 * BM + b * 32 + acc_row(lane, r);
-            if (row < M && col < N) {
-                double val = acc64[b][r];
-                if (sa != nullptr) val = ldexp(val, sa[row] + col_w);
-                C[row * ldc + col] = out_update(val, alpha, beta, C + row * ldc + col);
-            }
-        }
 }
 
 }  // namespace
@@ -279,11 +290,25 @@ template <int D>
 hipError_t launch_t64(const DgemmArgs &a, hipStream_t s) {
     constexpr int BM = t_bm(D);
     using K = CfgT<D, BM>;
-    if (a.KB % KB_PER_PANEL != 0 || a.RpadA % K::MT != 0 || a.RpadB % K::NT != 0)
+    if (a.KB < KB_PER_PANEL || a.KB % KB_PER_PANEL != 0 || a.RpadA % K::MT != 0 || a.RpadB % K::NT != 0)
         return hipErrorInvalidValue;
     const int nt_m = (int)((a.M + K::MT - 1) / K::MT), nt_n = (int)((a.N + K::NT - 1) / K::NT);
-    gemm_f64t_kernel<D, BM, 4, 8><<<nt_m * nt_n, 256, 0, s>>>(
-        a.Ap, a.Bp, a.C, a.M, a.N, (int)a.KB, a.RpadA, a.RpadB, a.ldc, a.sa, a.sb, a.alpha, a.beta, nt_m, nt_n);
+    const int ntiles = nt_m * nt_n, pw = persistent_workgroups();
+    // Reductions up to K = 2048, and d = 3 at any: one persistent workgroup per CU, so the next
+    // tile's first copies overlap a tile's epilogue and store, about 7 us per
+    // tile where the reduction of 512 itself takes 17 (d = 4; 16384 x 16384 x
+    // 512 with one workgroup per tile / persistent, ms: d = 3 2.44 / 2.09, d = 4 3.07 /
+    // 2.88, d = 5 4.61 / 4.00, d = 6 5.59 / 5.24; 8192 x 8192 x 2048 1-5 % less).
+    // Longer ones keep the dispatcher's balancing: persistent was 2-4 % slower
+    // at 8192^3 and 16384 x 8192 x 4096 for d = 4 .. 6, 1-3 % faster for d = 3.
+    if ((D == 3 || a.KB <= 64) && ntiles > pw)
+        gemm_f64t_kernel<D, BM, 4, 8, true><<<pw, 256, 0, s>>>(
+            a.Ap, a.Bp, a.C, a.M, a.N, (int)a.KB, a.RpadA, a.RpadB, a.ldc, a.sa, a.sb, a.alpha,
+            a.beta, nt_m, nt_n, ntiles);
+    else
+        gemm_f64t_kernel<D, BM, 4, 8, false><<<ntiles, 256, 0, s>>>(
+            a.Ap, a.Bp, a.C, a.M, a.N, (int)a.KB, a.RpadA, a.RpadB, a.ldc, a.sa, a.sb, a.alpha,
+            a.beta, nt_m, nt_n, ntiles);
     return hipGetLastError();
 }
 

@@ -260,22 +260,15 @@ __global__ __launch_bounds__(256, 1) void gemm_f64w_kernel(
             }
         }
 
-#pragma unroll
-        for (int e = 0; e < 2 * BMW; ++e) {
-            const int a = e / 2, b = e % 2;
-            const int64_t row0 = m0 + wm * 16 * BMW + a * 16 + (lane >> 4) * 4;
-            const int64_t col = n0 + wn * 32 + b * 16 + (lane & 15);
-            const int col_w = (sa != nullptr && col < N) ? sb[col] : 0;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t row = row0 + r;
-                if (row < M && col < N) {
-                    double val = acc64[e][r];
-                    if (sa != nullptr) val = ldexp(val, sa[row] + col_w);
-                    C[row * ldc + col] = out_update(val, alpha, beta, C + row * ldc + col);
-                }
-            }
-        }
+        // a column holds the 4 BMW values of BMW 16-row blocks (the lane is
+        // laundered as in gemm_f64_kernel)
+        int sl = lane;
+        if constexpr (PERSIST) asm volatile("" : "+v"(sl));
+        store_tile<2, 4 * BMW>(
+            [&](int b, int r) { return acc64[2 * (r / 4) + b][r % 4]; },
+            [&](int, int r) { return m0 + wm * 16 * BMW + (r / 4) * 16 + r % 4; }, (sl >> 4) * 4,
+            [&](int b) { return n0 + wn * 32 + b * 16; }, sl & 15,
+            m0 + K::MT <= M && n0 + K::NT <= N, M, N, C, ldc, alpha, beta, sa, sb);
     }
     // the last trips issued (unused) copies: let them land before the workgroup
     // ends and its LDS is handed to another workgroup
