@@ -83,10 +83,12 @@ struct F64ReplaySlot {
 struct alignas(64) F64SplitState {
     unsigned seen;                   // bit r: some block's maximum of level r has the
                                      // speculated exponent
-    unsigned ticket, done[6];        // replay work distribution (operand 0's are used)
     int v[6];                        // speculated chain
     int vfinal[6];
-    F64ReplaySlot slot[6];
+    // replay work distribution (operand 0's are used), each on cache lines of its own
+    alignas(64) unsigned ticket[16];
+    unsigned done[6];
+    alignas(64) F64ReplaySlot slot[6];
 };
 
 // One operand of an FP32 split launch.
