@@ -416,7 +416,7 @@ int emu_sgemm_ex(char transa, char transb, int64_t M, int64_t N, int64_t K, floa
         return EMU_OK;
     }
     const int tile_m = sgemm_tile_m(M, N, (K + KBLK - 1) / KBLK);
-    const Shape s = plan(M, N, K, 3, tile_m, SGEMM_NT);
+    const Shape s = plan(M, N, K, 3, tile_m, sgemm_tile_n(tile_m));
     // few output tiles: split the reduction (partial sums after the planes)
     const int splits = sgemm_splits(M, N, s.KB, tile_m);
     const size_t part_off = (s.bytesA + s.bytesB + 255) / 256 * 256;

@@ -32,7 +32,7 @@ constexpr int ROW_GROUP = 64;   // packed rows are padded to a multiple of this 
 constexpr int KPANEL = 256;     // reduction panel B_K of the FP32/FP64 reconstruction
 
 // ... and of the GEMM tile that reads them (output tile rows for A, columns for B).
-constexpr int SGEMM_NT = 128;   // SGEMM output tiles: (192 or 128) x 128
+constexpr int SGEMM_NT = 128;   // SGEMM output tiles: (192 or 128) x 128, or 64 x 64
 constexpr int DGEMM_NT = 64;
 // Slices of each operand that the products of depth d read (indices < 6).
 inline int dgemm_planes(int d) { return d < 6 ? d : 6; }
@@ -228,11 +228,12 @@ hipError_t launch_axpby_f64(const double *P, int64_t ldp, double *C, int64_t ldc
                             hipStream_t s);
 // alpha, beta: C = alpha P + beta C (see out_update); 1, 0 stores P
 // Split-K factor of the emulated SGEMM: 1 unless the output tiles fill at most
-// half of the chip, else up to 16 splits of whole reduction panels.  splits > 1 needs part:
+// half of the chip, else up to 16 (64-row tiles: 64) splits of whole reduction panels.  splits > 1 needs part:
 // splits x M x N floats of scratch for the partial sums.
 // CUs of the current device (256 on MI355X), read once per process.
 int device_cu_count();
-int sgemm_tile_m(int64_t M, int64_t N, int64_t KB);   // 192 or 128 output rows per tile
+int sgemm_tile_m(int64_t M, int64_t N, int64_t KB);   // 192, 128 or 64 output rows per tile
+int sgemm_tile_n(int tile_m);                          // its columns: 128, 128 or 64
 int sgemm_splits(int64_t M, int64_t N, int64_t KB, int tile_m);
 // The streamed-split SGEMM: op(A) op(B) read in FP32 by the GEMM, split per
 // k-block in the workgroup (128 x 128 tiles); same result bits as the split

@@ -216,6 +216,131 @@ __global__ __launch_bounds__(256, 1) void gemm_f32_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// The same products and accumulation on a 64 x 64 tile, for grids whose larger
+// tiles would leave CUs idle: 4 waves in a 2 x 2 grid, wave tile 32 x 32 (three
+// accumulator sets of 16 registers), 24 KB per k-block in a ring of three
+// stages, so two workgroups share a CU.  One barrier per k-block: a trip runs
+// its 12 MFMAs on fragments read in the trip before, reads the next k-block's
+// 12 fragments and issues the copies of the k-block three ahead.  It moves
+// 64 bytes per MFMA cycle where a CU's copies sustain about 50, so it is bound
+// by them; it wins where it replaces idle CUs or a split reduction.
+constexpr int SNT = 64, SNS = 3;
+constexpr int SGROUP = 3;                           // panels added up before the total
+constexpr int SPLANE = SNT * 64;                    // one plane of one operand, one k-block
+constexpr int SSTAGE = 2 * NC * SPLANE;
+constexpr int SCOPIES = SSTAGE / 1024 / 4;          // 1 KB copies per wave
+
+__global__ __launch_bounds__(256, 2) void gemm_f32_small_kernel(
+    const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Bp, float *__restrict__ C,
+    int64_t M, int64_t N, int KB, int64_t RpadA, int64_t RpadB, int64_t ldc, float alpha,
+    float beta, int nt_m, int nt_n, int kb_per_split, float *__restrict__ part) {
+    __shared__ __attribute__((aligned(1024))) char lds[SNS * SSTAGE];
+    int tm, tn;
+    tile_coords<4>(nt_m, nt_n, tm, tn);
+    const int lane = threadIdx.x & 63;
+    const unsigned lane16 = (unsigned)lane * 16u;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int64_t m0 = (int64_t)tm * SNT, n0 = (int64_t)tn * SNT;
+    const int kb_lo = blockIdx.y * kb_per_split;
+    const int kb_hi = min(KB, kb_lo + kb_per_split);
+
+    // Copy c by wave w moves 1 KB part w of A plane c (c < 3) or B plane c - 3.
+    const int64_t a_plane = plane_elems(KB, RpadA) * 2, b_plane = plane_elems(KB, RpadB) * 2;
+    const char *Ag = reinterpret_cast<const char *>(Ap) + m0 * 64 + wave * 1024;
+    const char *Bg = reinterpret_cast<const char *>(Bp) + n0 * 64 + wave * 1024;
+    auto issue_one = [&](int kb, char *dst, auto c_c) {
+        constexpr int c = decltype(c_c)::value;
+        if constexpr (c < NC)
+            copy_1k(Ag + (int64_t)kb * RpadA * 64 + c * a_plane, dst + c * SPLANE + wave * 1024, lane16);
+        else
+            copy_1k(Bg + (int64_t)kb * RpadB * 64 + (c - NC) * b_plane,
+                    dst + c * SPLANE + wave * 1024, lane16);
+    };
+    const int off0 = frag_offset(lane, 0), off1 = frag_offset(lane, 1);
+    struct Frags {
+        bf16x8 a[2][NC], b[2][NC];   // [sub-step][plane]
+    };
+    // read r: sub-step r / 6, operand planes interleaved (A0, B0, B1, B2, A1, A2)
+    auto read_one = [&](const char *base, Frags &f, auto r_c) {
+        constexpr int r = decltype(r_c)::value, s = r / 6, w = r % 6;
+        constexpr bool is_b = w >= 1 && w <= 3;
+        constexpr int p = is_b ? w - 1 : (w == 0 ? 0 : w - 3);
+        const int off = s ? off1 : off0;
+        if constexpr (is_b) f.b[s][p] = lds_frag(base + (NC + p) * SPLANE + wn * 32 * 64, off);
+        else f.a[s][p] = lds_frag(base + p * SPLANE + wm * 32 * 64, off);
+    };
+
+    f32x16 hi, lo, blk = f32x16{}, tot = f32x16{};
+    constexpr int PI[6] = {0, 0, 0, 1, 1, 2}, PJ[6] = {0, 1, 2, 0, 1, 0};
+    // Ring of SNS stages, k-block kb_lo + q in stage q mod SNS: trip q starts once
+    // every wave's copies of q + 1 have landed and every wave has read q.  The
+    // copies past the last k-block fetch the last one again (in bounds, unused).
+    auto stage = [&](int i) -> char * { return lds + i * SSTAGE; };
+    for (int j = 0; j < SNS; ++j)
+        static_for<SCOPIES>([&](auto c_c) { issue_one(min(kb_lo + j, kb_hi - 1), stage(j), c_c); });
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((SNS - 1) * SCOPIES) : "memory");
+    __syncthreads();
+    Frags f0, f1;
+    static_for<12>([&](auto r_c) { read_one(stage(0), f0, r_c); });
+    int qs = 0, kb = kb_lo;
+    auto trip = [&](const Frags &cur, Frags &nxt, auto zero_c, auto zero_lo_c) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((SNS - 2) * SCOPIES) : "memory");
+        pipeline_barrier();
+        const int qn = qs + 1 == SNS ? 0 : qs + 1, ckb = min(kb + SNS, kb_hi - 1);
+        static_for<12>([&](auto t_c) {
+            constexpr int t = decltype(t_c)::value, s = t / 6, g = t % 6;
+            if constexpr (g == 0)
+                hi = mfma(cur.a[s][0], cur.b[s][0], decltype(zero_c)::value && s == 0 ? f32x16{} : hi);
+            else
+                lo = mfma(cur.a[s][PI[g]], cur.b[s][PJ[g]],
+                          decltype(zero_lo_c)::value && t == 1 ? f32x16{} : lo);
+            order_fence();
+            read_one(stage(qn), nxt, t_c);
+            order_fence();
+            if constexpr (t % 2 == 0)
+                issue_one(ckb, stage(qs), std::integral_constant<int, t / 2>{});
+            order_fence();
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        qs = qn;
+        ++kb;
+    };
+    static_assert(SCOPIES == 6, "a copy every second slot");
+    // panels of eight k-blocks; every panel starts on f0
+    int group = 0;
+    for (int p0 = kb_lo; p0 < kb_hi; p0 += KB_PER_PANEL) {
+        const int p1 = min(kb_hi, p0 + KB_PER_PANEL);
+        if (p0 == kb_lo) trip(f0, f1, std::true_type{}, std::true_type{});
+        else trip(f0, f1, std::true_type{}, std::false_type{});
+        while (kb < p1) {
+            trip(f1, f0, std::false_type{}, std::false_type{});
+            if (kb < p1) trip(f0, f1, std::false_type{}, std::false_type{});
+        }
+        blk += hi;
+        // two levels: unsplit reductions of K = 1300 .. 3000 were 2-8 % further
+        // off than the split ones of a larger tile with one, 0-1 % nearer with two
+        if (++group == SGROUP) {
+            tot += blk;
+            blk = f32x16{};
+            group = 0;
+        }
+    }
+    tot += blk;
+    tot += lo;
+    // the last trips issued (unused) copies: let them land before the workgroup
+    // ends and its LDS is handed to another workgroup
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const bool whole = part == nullptr;
+    float *const dst = whole ? C : part + (int64_t)blockIdx.y * M * N;
+    store_tile<1, 16>([&](int, int r) { return tot[r]; },
+                      [&](int, int r) { return m0 + wm * 32 + acc_row(r); }, acc_lrow(lane),
+                      [&](int) { return n0 + wn * 32; }, lane & 31, m0 + SNT <= M && n0 + SNT <= N,
+                      M, N, dst, whole ? ldc : N, whole ? alpha : 1.0f, whole ? beta : 0.0f, nullptr,
+                      nullptr);
+}
+
+// ---------------------------------------------------------------------------
 // Streamed split (the alternative of Sec. 6.2 in which the components are made
 // where they are consumed): the same products, accumulation and tile walk as
 // gemm_f32_kernel, but the workgroup reads op(A) and op(B) in FP32 and splits
@@ -457,7 +582,16 @@ __global__ void reduce_splits_kernel(const float *__restrict__ part, int splits,
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
          i += (int64_t)gridDim.x * blockDim.x) {
         float p = part[i];
-        for (int sp = 1; sp < splits; ++sp) p += part[sp * total + i];
+        // eight loads in flight; the sums stay in split order
+        int sp = 1;
+        for (; sp + 8 <= splits; sp += 8) {
+            float x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = part[(sp + u) * total + i];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p += x[u];
+        }
+        for (; sp < splits; ++sp) p += part[sp * total + i];
         const int64_t row = i / N, col = i - row * N;
         C[row * ldc + col] =
             out_update(p, alpha, beta, beta != 0.0f ? C[row * ldc + col] : 0.0f);
@@ -466,38 +600,60 @@ __global__ void reduce_splits_kernel(const float *__restrict__ part, int splits,
 
 }  // namespace
 
+int sgemm_tile_n(int tile_m) { return tile_m == 64 ? SNT : NT; }
+
 int sgemm_splits(int64_t M, int64_t N, int64_t KB, int tile_m) {
     const int64_t cus = device_cu_count();
-    const int64_t tiles = ((M + tile_m - 1) / tile_m) * ((N + NT - 1) / NT);
+    const int tile_n = sgemm_tile_n(tile_m);
+    const int64_t tiles = ((M + tile_m - 1) / tile_m) * ((N + tile_n - 1) / tile_n);
     const int64_t panels = (KB + KB_PER_PANEL - 1) / KB_PER_PANEL;
     // split only when the tiles fill at most half of the CUs, and keep all
     // splits within one wave of workgroups (the partial sums cost a pass)
     if (2 * tiles > cus || panels < 2) return 1;
     int64_t sp = cus / tiles;
     sp = sp < panels ? sp : panels;
-    sp = sp < 16 ? sp : 16;
+    // (64-row tiles: up to 64 parts, which sum at most 4 MB per launch)
+    const int64_t most = tile_m == 64 ? 64 : 16;
+    sp = sp < most ? sp : most;
     const int64_t per = (panels + sp - 1) / sp;             // whole panels per split
     return (int)((panels + per - 1) / per);
 }
 
 int sgemm_tile_m(int64_t M, int64_t N, int64_t KB) {
-    // One workgroup per CU runs at a time (120 or 96 KB of LDS).  Model the
-    // time of each tile height as rounds of workgroups x rows per tile x
-    // k-blocks per split, the 128-row tile's larger copy share per MFMA counted
-    // as 5 %, and take the shorter (measured: 128 rows are 18-28 % faster at
-    // 2048^3 and 2560^3, 4-13 % at 1024^3, 4096^3 and 1024 x 1024 x 65536;
-    // 192 rows 2-19 % faster at 3072^3, 6144^3, 16384 x 16384 x 512 and
-    // 3000 x 2000 x 4000).
-    const int64_t cus = device_cu_count();
+    // Modelled time of each tile (us, fitted to MI355X): a k-block takes 1.13,
+    // 0.80 or 0.33 on a CU that runs one workgroup of 192, 128 or 64 rows, and
+    // 0.58 where it runs two of the last; fill and store of the large tiles
+    // cost 6 and 4 more, split partial sums a launch and their traffic.
+    // Measured calls, 192 / 128 / 64 rows, us: 512^3 26.4 / 19.3 / 16.0, 1111 x 777 x
+    // 1501 39.5 / 36.2 / 31.5, 1024^3 33.6 / 30.5 / 26.9, 1500^3 59.9 / 58.3 /
+    // 60.6, 2048^3 116 / 97 / 110, 3000 x 3000 x 500 70.3 / 73.3 / 69.4, 500 x 500 x
+    // 5000 49 / 42 / 38, 1024 x 1024 x 65536 964 / 928 / 1139; 192 rows are
+    // 2-19 % faster than 128 at 3072^3, 6144^3 and 16384 x 16384 x 512.
+    const int64_t cus = device_cu_count(), panels = (KB + KB_PER_PANEL - 1) / KB_PER_PANEL;
+    const int64_t sp128 = sgemm_splits(M, N, KB, 128);
     double best = 0.0;
-    int pick = 192;
-    for (int t : {192, 128}) {
-        const int64_t tiles = ((M + t - 1) / t) * ((N + NT - 1) / NT);
-        const int64_t sp = sgemm_splits(M, N, KB, t);
-        const int64_t rounds = (tiles * sp + cus - 1) / cus;
-        const double cost = (double)rounds * t * (double)((KB + sp - 1) / sp) * (t == 128 ? 1.05 : 1.0);
-        if (t == 192 || cost < best) {
-            best = cost;
+    int pick = 0;
+    for (int t : {192, 128, 64}) {
+        const int tile_n = sgemm_tile_n(t);
+        const int64_t sp = sgemm_splits(M, N, KB, t), per = (panels + sp - 1) / sp;
+        // The 64-row tile adds its panels in groups: it is not taken where it
+        // would cut the reduction like the streamed split (128 rows) does, whose
+        // bits are then the same, and a part has more panels than a group.
+        if (t == 64 && sp == sp128 && per > SGROUP) continue;
+        const int64_t wg = ((M + t - 1) / t) * ((N + tile_n - 1) / tile_n) * sp;
+        const double kb = sp > 1 ? (double)(per * KB_PER_PANEL) : (double)KB;
+        double us;
+        if (t == 64) {
+            const int64_t rem = wg % (2 * cus);
+            us = (double)(wg / (2 * cus)) * 0.58;
+            if (rem > 0) us += 0.33 + (rem > cus ? 0.25 * (double)(rem - cus) / (double)cus : 0.0);
+            us *= kb;
+        } else {
+            us = (double)((wg + cus - 1) / cus) * kb * (t == 192 ? 1.13 : 0.80) + (t == 192 ? 6.0 : 4.0);
+        }
+        if (sp > 1) us += 4.0 + (double)sp * (double)M * (double)N * 8.0 / 6e6;
+        if (pick == 0 || us < best) {
+            best = us;
             pick = t;
         }
     }
@@ -507,20 +663,20 @@ int sgemm_tile_m(int64_t M, int64_t N, int64_t KB) {
 hipError_t launch_gemm_f32(const uint16_t *Ap, const uint16_t *Bp, float *C, int64_t M, int64_t N,
                            int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc, float alpha,
                            float beta, int tile_m, int splits, float *part, hipStream_t s) {
-    if (tile_m != 192 && tile_m != 128) return hipErrorInvalidValue;
-    const int nt_m = (int)((M + tile_m - 1) / tile_m), nt_n = (int)((N + NT - 1) / NT);
+    if (tile_m != 192 && tile_m != 128 && tile_m != 64) return hipErrorInvalidValue;
+    const int tile_n = sgemm_tile_n(tile_m);
+    const int nt_m = (int)((M + tile_m - 1) / tile_m), nt_n = (int)((N + tile_n - 1) / tile_n);
     const int64_t panels = (KB + KB_PER_PANEL - 1) / KB_PER_PANEL;
     const int kb_per_split = (int)((panels + splits - 1) / splits) * KB_PER_PANEL;
     if (splits < 1 || (splits > 1 && !part) || (int64_t)(splits - 1) * kb_per_split >= KB)
         return hipErrorInvalidValue;
     const dim3 grid(nt_m * nt_n, splits);
     float *pp = splits > 1 ? part : nullptr;
-    if (tile_m == 192)
-        gemm_f32_kernel<3><<<grid, 256, 0, s>>>(Ap, Bp, C, M, N, (int)KB, RpadA, RpadB, ldc, alpha,
-                                                beta, nt_m, nt_n, kb_per_split, pp);
-    else
-        gemm_f32_kernel<2><<<grid, 256, 0, s>>>(Ap, Bp, C, M, N, (int)KB, RpadA, RpadB, ldc, alpha,
-                                                beta, nt_m, nt_n, kb_per_split, pp);
+    auto *kernel = tile_m == 192   ? gemm_f32_kernel<3>
+                   : tile_m == 128 ? gemm_f32_kernel<2>
+                                   : gemm_f32_small_kernel;
+    kernel<<<grid, 256, 0, s>>>(Ap, Bp, C, M, N, (int)KB, RpadA, RpadB, ldc, alpha, beta, nt_m,
+                                nt_n, kb_per_split, pp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || splits == 1) return e;
     const int64_t total = M * N;
