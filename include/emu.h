@@ -186,9 +186,9 @@ int emu_dgemm_ex(char transa, char transb, int64_t M, int64_t N, int64_t K, doub
    overflowed slice, a panel product that may be inexact in FP32), C is
    recomputed as alpha op(A) op(B) + beta C by a plain FP64 GEMM (fused
    multiply-adds, its own summation order) and EMU_STATUS_FALLBACK is reported
-   as well.  The decision is taken on the device: no host synchronisation; the
-   armed mode costs a kernel launch per call that does nothing unless the
-   fallback is needed, plus, for beta != 0, a copy of C in the workspace.
+   as well.  The decision is taken on the device, before the product GEMM, which
+   is then left out: no host synchronisation; the armed mode costs a kernel
+   launch per call that does nothing unless the fallback is needed.
    EMU_EINVAL for any other value. */
 #define EMU_FALLBACK_NONE 0
 #define EMU_FALLBACK_FP64 1

@@ -463,14 +463,13 @@ DgemmOpts current_opts() {
 }
 
 // Workspace areas of one emulated DGEMM after the header: packed planes, then
-// (256-byte aligned) the weights of the scale-aware split, then a copy of C
-// for a fallback that must still read beta C.
+// (256-byte aligned) the weights of the scale-aware split.
 struct DgemmLayout {
     Shape s;
-    size_t scale_off, csave_off, bytes;
+    size_t scale_off, bytes;
 };
 
-DgemmLayout dgemm_layout(int64_t M, int64_t N, int64_t K, int d, DgemmOpts o, double beta) {
+DgemmLayout dgemm_layout(int64_t M, int64_t N, int64_t K, int d, DgemmOpts o) {
     DgemmLayout L;
     // the DGEMM kernel's tile rows and k-block multiple (padding is zero)
     const int64_t KB = (K + KBLK - 1) / KBLK;
@@ -478,8 +477,7 @@ DgemmLayout dgemm_layout(int64_t M, int64_t N, int64_t K, int d, DgemmOpts o, do
                dgemm_kb_padded(d, M, N, KB));
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     L.scale_off = up(L.s.bytesA + L.s.bytesB);
-    L.csave_off = up(L.scale_off + (o.scaled ? scale_bytes(M, N) : 0));
-    L.bytes = L.csave_off + ((o.fallback && beta != 0.0) ? (size_t)M * N * sizeof(double) : 0);
+    L.bytes = up(L.scale_off + (o.scaled ? scale_bytes(M, N) : 0));
     return L;
 }
 
@@ -490,19 +488,20 @@ unsigned *ws_call_status(char *base) { return reinterpret_cast<unsigned *>(base 
 // The emulated DGEMM on a workspace at base (header, planes, weights), after
 // argument validation; M, N, K > 0 and alpha != 0.  status_to: the word the
 // split's flags go to when the fallback is not armed (null: the accumulated
-// word).
+// word).  skip_if: the word of a fallback armed by the caller, which makes the
+// product GEMM unneeded once it is nonzero (its own word where o.fallback).
 int dgemm_run(char *base, DgemmOpts o, bool ta, bool tb, int64_t M, int64_t N, int64_t K,
               double alpha, const double *A, int64_t lda, const double *B, int64_t ldb,
-              double beta, double *C, int64_t ldc, int d, unsigned *status_to = nullptr) {
+              double beta, double *C, int64_t ldc, int d, unsigned *status_to = nullptr,
+              const unsigned *skip_if = nullptr) {
     // Only the slices the retained products read are materialised; the levels
     // after them never influence the earlier slices.
     const int np = dgemm_planes(d);
-    const DgemmLayout L = dgemm_layout(M, N, K, d, o, beta);
+    const DgemmLayout L = dgemm_layout(M, N, K, d, o);
     const Shape &s = L.s;
     uint16_t *Ap = ws_planes(base, 0), *Bp = ws_planes(base, s.bytesA);
     F64SplitState *st = ws_states(base);
     const ScaleArea sc = ws_scales(base, L.scale_off, M, N);
-    double *Csave = reinterpret_cast<double *>(base + HDR + L.csave_off);
     // stored shapes: A is M x K ('N') or K x M ('T'); B is K x N ('N') or N x K ('T')
     const int64_t ar = ta ? K : M, ac = ta ? M : K, br = tb ? N : K, bc = tb ? K : N;
     prof_mark(0);
@@ -533,17 +532,15 @@ int dgemm_run(char *base, DgemmOpts o, bool ta, bool tb, int64_t M, int64_t N, i
     e = launch_split_f64(ops, 2, s.KB, np, g_split_mode, d, split_status, g_stream);
     if (e != hipSuccess) return hip_fail(e, "split_f64");
     prof_mark(1);
-    const bool save_c = o.fallback && beta != 0.0;
-    if (save_c) {
-        e = launch_copy_matrix_f64(C, ldc, Csave, N, M, N, g_stream);
-        if (e != hipSuccess) return hip_fail(e, "save C");
-    }
+    // all flags of the call are known here: where the fallback is going to compute
+    // C, the product GEMM leaves it alone (so beta C is still there to read)
     e = launch_gemm_f64(Ap, Bp, C, M, N, s.KB, s.RpadA, s.RpadB, ldc, o.scaled ? sc.sa : nullptr,
-                        o.scaled ? sc.sb : nullptr, alpha, beta, d, g_stream);
+                        o.scaled ? sc.sb : nullptr, alpha, beta, d,
+                        o.fallback ? split_status : skip_if, g_stream);
     if (e != hipSuccess) return hip_fail(e, "gemm_f64");
     if (o.fallback) {
         e = launch_fallback_dgemm(split_status, ws_status(base), M, N, K, alpha, A, lda, ta, B, ldb,
-                                  tb, beta, save_c ? Csave : C, save_c ? N : ldc, C, ldc, g_stream);
+                                  tb, beta, C, ldc, g_stream);
         if (e != hipSuccess) return hip_fail(e, "fallback_dgemm");
     }
     prof_mark(2);
@@ -567,7 +564,7 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
     const bool direct = alpha == 1.0 && beta == 0.0;
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     // workspace after the area of the largest group's DGEMM (its planes and weights)
-    size_t off = up(dgemm_layout(M, N, K, d, {true, false}, 0.0).bytes);
+    size_t off = up(dgemm_layout(M, N, K, d, {true, false}).bytes);
     const int64_t MN = M > N ? M : N;
     const size_t o_sa = off;  off = up(off + (size_t)M * 4);
     const size_t o_sb = off;  off = up(off + (size_t)N * 4);
@@ -631,13 +628,13 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
                                g_stream);
         if (e != hipSuccess) return hip_fail(e, "kbin gather");
         rc = dgemm_run(base, {true, false}, false, false, M, N, kb, 1.0, GA, kb, GB, N,
-                       g == 0 ? 0.0 : 1.0, T, ldt, d, fb ? call_st : acc_st);
+                       g == 0 ? 0.0 : 1.0, T, ldt, d, fb ? call_st : acc_st, fb ? call_st : nullptr);
         if (rc) return rc;
     }
     if (fb) {
         // C is untouched unless direct (then beta = 0 and C is not read)
-        e = launch_fallback_dgemm(call_st, acc_st, M, N, K, alpha, A, lda, ta, B, ldb, tb, beta,
-                                  C, ldc, C, ldc, g_stream);
+        e = launch_fallback_dgemm(call_st, acc_st, M, N, K, alpha, A, lda, ta, B, ldb, tb, beta, C,
+                                  ldc, g_stream);
         if (e != hipSuccess) return hip_fail(e, "fallback_dgemm");
     }
     if (!direct) {
@@ -686,7 +683,7 @@ int emu_dgemm_ex(char transa, char transb, int64_t M, int64_t N, int64_t K, doub
     if (g_split_scope == EMU_SCOPE_KBIN)
         return dgemm_kbin(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, d);
     const DgemmOpts o = current_opts();
-    rc = ensure_workspace(dgemm_layout(M, N, K, d, o, beta).bytes);
+    rc = ensure_workspace(dgemm_layout(M, N, K, d, o).bytes);
     if (rc) return rc;
     return dgemm_run(g_ws.base, o, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, d);
 }
@@ -701,7 +698,7 @@ int emu_dgemm_noalloc(int64_t M, int64_t N, int64_t K, const double *A, int64_t 
     if (g_split_scope == EMU_SCOPE_KBIN)
         return fail(EMU_EINVAL, "emu_dgemm_noalloc: the K-binned scope needs the growing workspace");
     const DgemmOpts o = current_opts();
-    const size_t need = HDR + dgemm_layout(M, N, K, d, o, 0.0).bytes;
+    const size_t need = HDR + dgemm_layout(M, N, K, d, o).bytes;
     if (need > NOALLOC_BYTES) {
         g_err = "emu_dgemm_noalloc: this problem needs " + std::to_string(need) +
                 " bytes of scratch, more than the fixed " + std::to_string(NOALLOC_BYTES);

@@ -202,15 +202,12 @@ hipError_t launch_scale_exponents(const double *X, int64_t rows, int64_t cols, i
 hipError_t launch_unpack(const uint16_t *P, int nc, int64_t KB, int64_t Rpad, int64_t rows,
                          int64_t cols, bool as_b, uint16_t *out, hipStream_t s);
 hipError_t launch_copy_v(const F64SplitState *st, int32_t *v, hipStream_t s);
-// Native FP64 fallback: C = alpha op(A) op(B) + beta Cin when *call_status is
+// Native FP64 fallback: C = alpha op(A) op(B) + beta C when *call_status is
 // nonzero (then also status |= *call_status | ST_FALLBACK); nothing otherwise.
 hipError_t launch_fallback_dgemm(const unsigned *call_status, unsigned *status, int64_t M,
                                  int64_t N, int64_t K, double alpha, const double *A, int64_t lda,
                                  bool ta, const double *B, int64_t ldb, bool tb, double beta,
-                                 const double *Cin, int64_t ldcin, double *C, int64_t ldc,
-                                 hipStream_t s);
-hipError_t launch_copy_matrix_f64(const double *src, int64_t lds, double *dst, int64_t ldd,
-                                  int64_t M, int64_t N, hipStream_t s);
+                                 double *C, int64_t ldc, hipStream_t s);
 // K-binned scope: the class of every reduction index of op(A) op(B) (-1: left
 // out) from the ROWCOL weights sa, sb; ma, mb: K 64-bit words of scratch each.
 constexpr int KBIN_WIDTH = 8, KBIN_MAX = 8;
@@ -252,9 +249,10 @@ hipError_t launch_gemm_f32(const uint16_t *Ap, const uint16_t *Bp, float *C, int
 int64_t dgemm_tile_rows(int d, int64_t M, int64_t N, int64_t KB);
 int64_t dgemm_kb_padded(int d, int64_t M, int64_t N, int64_t KB);
 // sa, sb: row weights of A and column weights of B to restore (C_mn times
-// 2^(sa_m + sb_n)), or both null
+// 2^(sa_m + sb_n)), or both null; skip_if: a word that, when nonzero, makes the
+// launch do nothing (the fallback is going to compute C), or null
 hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, int64_t M,
                            int64_t N, int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
                            const int *sa, const int *sb, double alpha, double beta, int d,
-                           hipStream_t s);
+                           const unsigned *skip_if, hipStream_t s);
 }  // namespace emu

@@ -63,8 +63,8 @@ __device__ inline void store_slab(const SlabRegs &r, double (*As)[FP], double (*
 __global__ __launch_bounds__(256) void fallback_dgemm_kernel(
     const unsigned *__restrict__ call_status, unsigned *__restrict__ status, int64_t M, int64_t N,
     int64_t K, double alpha, const double *__restrict__ A, int64_t lda, int ta,
-    const double *__restrict__ B, int64_t ldb, int tb, double beta, const double *__restrict__ Cin,
-    int64_t ldcin, double *__restrict__ C, int64_t ldc) {
+    const double *__restrict__ B, int64_t ldb, int tb, double beta, double *__restrict__ C,
+    int64_t ldc) {
     const unsigned flags = *call_status;
     if (flags == 0u) return;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) atomicOr(status, flags | ST_FALLBACK);
@@ -119,15 +119,9 @@ __global__ __launch_bounds__(256) void fallback_dgemm_kernel(
                 const int64_t m = m0 + wm * 32 + i * 16 + fk + 4 * q;
                 if (m < M && n < N)
                     C[m * ldc + n] = out_update(acc[i][j][q], alpha, beta,
-                                                beta != 0.0 ? Cin[m * ldcin + n] : 0.0);
+                                                beta != 0.0 ? C[m * ldc + n] : 0.0);
             }
         }
-}
-
-__global__ void copy_matrix_f64_kernel(const double *__restrict__ src, int64_t lds,
-                                       double *__restrict__ dst, int64_t ldd, int64_t M, int64_t N) {
-    for (int64_t r = blockIdx.x; r < M; r += gridDim.x)
-        for (int64_t c = threadIdx.x; c < N; c += blockDim.x) dst[r * ldd + c] = src[r * lds + c];
 }
 
 }  // namespace
@@ -135,20 +129,11 @@ __global__ void copy_matrix_f64_kernel(const double *__restrict__ src, int64_t l
 hipError_t launch_fallback_dgemm(const unsigned *call_status, unsigned *status, int64_t M,
                                  int64_t N, int64_t K, double alpha, const double *A, int64_t lda,
                                  bool ta, const double *B, int64_t ldb, bool tb, double beta,
-                                 const double *Cin, int64_t ldcin, double *C, int64_t ldc,
-                                 hipStream_t s) {
+                                 double *C, int64_t ldc, hipStream_t s) {
     const dim3 grid((unsigned)((N + FT - 1) / FT), (unsigned)((M + FT - 1) / FT));
     if (grid.y > 65535) return hipErrorInvalidValue;
     fallback_dgemm_kernel<<<grid, 256, 0, s>>>(call_status, status, M, N, K, alpha, A, lda,
-                                               ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, Cin, ldcin, C,
-                                               ldc);
-    return hipGetLastError();
-}
-
-hipError_t launch_copy_matrix_f64(const double *src, int64_t lds, double *dst, int64_t ldd,
-                                  int64_t M, int64_t N, hipStream_t s) {
-    const int g = (int)(M < 4096 ? M : 4096);
-    copy_matrix_f64_kernel<<<g, 256, 0, s>>>(src, lds, dst, ldd, M, N);
+                                               ta ? 1 : 0, B, ldb, tb ? 1 : 0, beta, C, ldc);
     return hipGetLastError();
 }
 

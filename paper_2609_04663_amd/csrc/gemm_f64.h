@@ -28,13 +28,15 @@ constexpr int n_prod(int d) {
 }
 
 // One product GEMM on packed operands: C (M x N, ldc) = alpha P + beta C over KB
-// k-blocks; sa, sb: row and column weights to restore, or both null.
+// k-blocks; sa, sb: row and column weights to restore, or both null.  skip_if:
+// when not null, the kernel does nothing (and leaves C) if *skip_if is nonzero.
 struct DgemmArgs {
     const uint16_t *Ap, *Bp;
     double *C;
     int64_t M, N, KB, RpadA, RpadB, ldc;
     const int *sa, *sb;
     double alpha, beta;
+    const unsigned *skip_if;
 };
 
 // Persistent grid of the DGEMM kernels: one workgroup per CU (their LDS use

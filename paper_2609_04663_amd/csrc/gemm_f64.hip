@@ -58,7 +58,7 @@ int64_t dgemm_kb_padded(int d, int64_t M, int64_t N, int64_t KB) {
 hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, int64_t M,
                            int64_t N, int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
                            const int *sa, const int *sb, double alpha, double beta, int d,
-                           hipStream_t s) {
+                           const unsigned *skip_if, hipStream_t s) {
     // Depths 1 .. 5 take the wide kernel's 64 x 64 tiles (BMW = 2) where it
     // measured faster than the 32 x 32 x 16 kernel: long reductions (K > 1024)
     // of d = 2, 4 and 5 (8, 2 and 5 % at 8192^3), and grids of d = 1 .. 3
@@ -67,7 +67,8 @@ hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, in
     // 128 x 64 tiles (BMW = 4; 7-40 % faster).  Short reductions of d = 1, 2,
     // 4, 5 and the large grids of d = 3 measured faster on the 32 x 32 x 16
     // kernel.  Both kernels give the same bits.
-    const DgemmArgs a = {Ap, Bp, C, M, N, KB, RpadA, RpadB, ldc, sa, sb, alpha, beta};
+    const DgemmArgs a = {Ap, Bp, C, M, N, KB, RpadA, RpadB, ldc, sa, sb, alpha, beta,
+                         skip_if};
     const int pw = persistent_workgroups();
     auto few_tiles = [&](int64_t mt) {
         return ((M + mt - 1) / mt) * ((N + DGEMM_NT - 1) / DGEMM_NT) < pw;

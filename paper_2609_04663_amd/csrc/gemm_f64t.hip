@@ -101,7 +101,8 @@ __global__ __launch_bounds__(256, 1) void gemm_f64t_kernel(
     const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Bp, double *__restrict__ C,
     int64_t M, int64_t N, int KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
     const int *__restrict__ sa, const int *__restrict__ sb, double alpha, double beta, int nt_m,
-    int nt_n, int ntiles) {
+    int nt_n, int ntiles, const unsigned *__restrict__ skip_if) {
+    if (skip_if != nullptr && *skip_if != 0u) return;
     using K = CfgT<D, BM>;
     constexpr int P = K::P, NPL = K::NPL, NS = K::NS, T = K::T;
     using SC = SchedOf<D, BM, W0, W1>;
@@ -304,11 +305,11 @@ hipError_t launch_t64(const DgemmArgs &a, hipStream_t s) {
     if ((D == 3 || a.KB <= 64) && ntiles > pw)
         gemm_f64t_kernel<D, BM, 4, 8, true><<<pw, 256, 0, s>>>(
             a.Ap, a.Bp, a.C, a.M, a.N, (int)a.KB, a.RpadA, a.RpadB, a.ldc, a.sa, a.sb, a.alpha,
-            a.beta, nt_m, nt_n, ntiles);
+            a.beta, nt_m, nt_n, ntiles, a.skip_if);
     else
         gemm_f64t_kernel<D, BM, 4, 8, false><<<ntiles, 256, 0, s>>>(
             a.Ap, a.Bp, a.C, a.M, a.N, (int)a.KB, a.RpadA, a.RpadB, a.ldc, a.sa, a.sb, a.alpha,
-            a.beta, nt_m, nt_n, ntiles);
+            a.beta, nt_m, nt_n, ntiles, a.skip_if);
     return hipGetLastError();
 }
 

@@ -65,7 +65,8 @@ __global__ __launch_bounds__(256, 1) void gemm_f64w_kernel(
     const uint16_t *__restrict__ Ap, const uint16_t *__restrict__ Bp, double *__restrict__ C,
     int64_t M, int64_t N, int KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
     const int *__restrict__ sa, const int *__restrict__ sb, double alpha, double beta, int nt_m,
-    int nt_n, int ntiles) {
+    int nt_n, int ntiles, const unsigned *__restrict__ skip_if) {
+    if (skip_if != nullptr && *skip_if != 0u) return;
     using K = CfgW<D, NS, ACC64_LDS, BMW>;
     __shared__ __attribute__((aligned(1024))) char lds[NS * K::STAGE + K::ACC64_BYTES];
     // lane-private FP64 accumulators in LDS: element e = 4 (2 a + b) + r of
@@ -295,12 +296,12 @@ hipError_t launch_w(const DgemmArgs &a, hipStream_t s) {
         if (a.KB % 2 == 0 && a.KB <= 32 && ntiles > pw) {
             gemm_f64w_kernel<D, NS, ACC64_LDS, true, BMW><<<pw, 256, 0, s>>>(
                 a.Ap, a.Bp, a.C, a.M, a.N, (int)a.KB, a.RpadA, a.RpadB, a.ldc, a.sa, a.sb, a.alpha, a.beta, nt_m, nt_n,
-                ntiles);
+                ntiles, a.skip_if);
             return hipGetLastError();
         }
     }
     gemm_f64w_kernel<D, NS, ACC64_LDS, false, BMW><<<ntiles, 256, 0, s>>>(
-        a.Ap, a.Bp, a.C, a.M, a.N, (int)a.KB, a.RpadA, a.RpadB, a.ldc, a.sa, a.sb, a.alpha, a.beta, nt_m, nt_n, ntiles);
+        a.Ap, a.Bp, a.C, a.M, a.N, (int)a.KB, a.RpadA, a.RpadB, a.ldc, a.sa, a.sb, a.alpha, a.beta, nt_m, nt_n, ntiles, a.skip_if);
     return hipGetLastError();
 }
 
