@@ -456,10 +456,11 @@ namespace {
 struct DgemmOpts {
     bool scaled;
     bool fallback;
+    bool stats_ready = false;   // (scaled) the magnitude statistics are in place
 };
 
 DgemmOpts current_opts() {
-    return {g_split_scope != EMU_SCOPE_OPERAND, g_fallback == EMU_FALLBACK_FP64};
+    return {g_split_scope != EMU_SCOPE_OPERAND, g_fallback == EMU_FALLBACK_FP64, false};
 }
 
 // Workspace areas of one emulated DGEMM after the header: packed planes, then
@@ -479,6 +480,12 @@ DgemmLayout dgemm_layout(int64_t M, int64_t N, int64_t K, int d, DgemmOpts o) {
     L.scale_off = up(L.s.bytesA + L.s.bytesB);
     L.bytes = up(L.scale_off + (o.scaled ? scale_bytes(M, N) : 0));
     return L;
+}
+
+// The smallest magnitudes of an operand's packed rows (8 bytes of the 64 that
+// plane 0 has for each row of a k-block), until the split writes the planes.
+unsigned long long *mag_min(uint16_t *planes) {
+    return reinterpret_cast<unsigned long long *>(planes);
 }
 
 // The accumulated status word (offset 0 of a workspace header) and the word of
@@ -516,19 +523,22 @@ int dgemm_run(char *base, DgemmOpts o, bool ta, bool tb, int64_t M, int64_t N, i
         if (e != hipSuccess) return hip_fail(e, "clear call status");
     }
     if (o.scaled) {
-        // weights: rows of op(A), columns of op(B) (the scale-aware split)
-        e = launch_scale_exponents(A, ar, ac, lda, ta, sc.mb, sc.sa, g_stream);
-        if (e != hipSuccess) return hip_fail(e, "scale_exponents(A)");
-        e = launch_scale_exponents(B, br, bc, ldb, !tb, sc.mb + M, sc.sb, g_stream);
-        if (e != hipSuccess) return hip_fail(e, "scale_exponents(B)");
+        // magnitudes of op(A)'s rows and op(B)'s columns (the split makes the
+        // weights of them); the smallest ones wait in the planes
+        if (!o.stats_ready) {
+            e = launch_mag_stats(A, ar, ac, lda, ta, sc.mb, mag_min(Ap), split_status, g_stream);
+            if (e != hipSuccess) return hip_fail(e, "mag_stats(A)");
+            e = launch_mag_stats(B, br, bc, ldb, !tb, sc.mb + M, mag_min(Bp), split_status, g_stream);
+            if (e != hipSuccess) return hip_fail(e, "mag_stats(B)");
+        }
     }
     // both operands in one launch per phase: op(A)'s rows are A's rows ('N') or
     // A's columns ('T', packed as a B operand), op(B)'s columns likewise
     const F64SplitOperand ops[2] = {
-        {A, ar, ac, lda, ta ? 1 : 0, o.scaled ? sc.sa : nullptr, Ap, s.RpadA,
-         s.RliveA, st},
-        {B, br, bc, ldb, tb ? 0 : 1, o.scaled ? sc.sb : nullptr, Bp, s.RpadB,
-         s.RliveB, st + 1}};
+        {A, ar, ac, lda, ta ? 1 : 0, o.scaled ? sc.sa : nullptr, sc.mb, mag_min(Ap), Ap,
+         s.RpadA, s.RliveA, st},
+        {B, br, bc, ldb, tb ? 0 : 1, o.scaled ? sc.sb : nullptr, sc.mb + M,
+         mag_min(Bp), Bp, s.RpadB, s.RliveB, st + 1}};
     e = launch_split_f64(ops, 2, s.KB, np, g_split_mode, d, split_status, g_stream);
     if (e != hipSuccess) return hip_fail(e, "split_f64");
     prof_mark(1);
@@ -547,10 +557,8 @@ int dgemm_run(char *base, DgemmOpts o, bool ta, bool tb, int64_t M, int64_t N, i
     return EMU_OK;
 }
 
-std::vector<int> g_kbin_idx;   // host copy of the K-binned index lists
-
 // The K-binned scope: classes of the reduction indices on the device, one
-// stream synchronisation to read them, then for every class in ascending
+// stream synchronisation to read their sizes, then for every class in ascending
 // order the gather of its columns of op(A) and rows of op(B) and a row/column
 // scaled emulated DGEMM of the group, added in FP64 to the previous groups'
 // sum (the first group stores, the others use the beta = 1 update, which adds
@@ -564,14 +572,14 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
     const bool direct = alpha == 1.0 && beta == 0.0;
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     // workspace after the area of the largest group's DGEMM (its planes and weights)
-    size_t off = up(dgemm_layout(M, N, K, d, {true, false}).bytes);
+    size_t off = up(dgemm_layout(M, N, K, d, {true, false, false}).bytes);
     const int64_t MN = M > N ? M : N;
     const size_t o_sa = off;  off = up(off + (size_t)M * 4);
     const size_t o_sb = off;  off = up(off + (size_t)N * 4);
     const size_t o_mx = off;  off = up(off + (size_t)MN * 8);
     const size_t o_ma = off;  off = up(off + (size_t)K * 8);
     const size_t o_mb = off;  off = up(off + (size_t)K * 8);
-    const size_t o_cl = off;  off = up(off + (size_t)K * 4);
+    const size_t o_cn = off;  off = up(off + KBIN_MAX * 4);
     const size_t o_ix = off;  off = up(off + (size_t)K * 4);
     const size_t o_ga = off;  off = up(off + (size_t)M * K * 8);
     const size_t o_gb = off;  off = up(off + (size_t)K * N * 8);
@@ -583,7 +591,7 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
     auto *mx = reinterpret_cast<unsigned long long *>(w + o_mx);
     auto *ma = reinterpret_cast<unsigned long long *>(w + o_ma);
     auto *mb = reinterpret_cast<unsigned long long *>(w + o_mb);
-    int *cls = reinterpret_cast<int *>(w + o_cl), *idx = reinterpret_cast<int *>(w + o_ix);
+    int *counts = reinterpret_cast<int *>(w + o_cn), *idx = reinterpret_cast<int *>(w + o_ix);
     double *GA = reinterpret_cast<double *>(w + o_ga), *GB = reinterpret_cast<double *>(w + o_gb);
     double *P = reinterpret_cast<double *>(w + o_p);
     unsigned *acc_st = ws_status(base), *call_st = ws_call_status(base);
@@ -596,38 +604,37 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
     e = launch_scale_exponents(A, ar, ac, lda, ta, mx, sa, g_stream);
     if (e == hipSuccess) e = launch_scale_exponents(B, br, bc, ldb, !tb, mx, sb, g_stream);
     if (e == hipSuccess)
-        e = launch_kbin_classes(A, lda, ta, B, ldb, tb, M, N, K, sa, sb, ma, mb, KBIN_WIDTH,
-                                KBIN_MAX, cls, g_stream);
+        e = launch_kbin_classes(A, lda, ta, B, ldb, tb, M, N, K, sa, sb, ma, mb, counts, idx,
+                                g_stream);
     if (e != hipSuccess) return hip_fail(e, "kbin classes");
-    std::vector<int> h((size_t)K);
-    e = hipMemcpyAsync(h.data(), cls, (size_t)K * 4, hipMemcpyDeviceToHost, g_stream);
+    int h[KBIN_MAX];   // the group sizes decide the launches
+    e = hipMemcpyAsync(h, counts, sizeof(h), hipMemcpyDeviceToHost, g_stream);
     if (e == hipSuccess) e = hipStreamSynchronize(g_stream);
     if (e != hipSuccess) return hip_fail(e, "kbin classes to the host");
-    // the index lists stay alive in g_kbin_idx until the next call, which
-    // synchronises the stream before it rewrites them
-    std::vector<int> &ks = g_kbin_idx;
-    ks.clear();
-    std::vector<std::pair<size_t, int64_t>> groups;   // (first index in ks, size)
+    std::vector<std::pair<size_t, int64_t>> groups;   // (first index in idx, size)
+    size_t first = 0;
     for (int c = 0; c < KBIN_MAX; ++c) {
-        const size_t first = ks.size();
-        for (int64_t k = 0; k < K; ++k)
-            if (h[(size_t)k] == c) ks.push_back((int)k);
-        if (ks.size() > first) groups.emplace_back(first, (int64_t)(ks.size() - first));
+        if (h[c] > 0) groups.emplace_back(first, (int64_t)h[c]);
+        first += (size_t)h[c];
     }
     if (groups.empty()) {   // every product term is an exact zero
         e = launch_scale_c_f64(C, M, N, ldc, beta, g_stream);
         return e == hipSuccess ? EMU_OK : hip_fail(e, "scale C");
     }
-    e = hipMemcpyAsync(idx, ks.data(), ks.size() * 4, hipMemcpyHostToDevice, g_stream);
-    if (e != hipSuccess) return hip_fail(e, "kbin index upload");
     double *T = direct ? C : P;
     const int64_t ldt = direct ? ldc : N;
     for (size_t g = 0; g < groups.size(); ++g) {
         const int64_t kb = groups[g].second;
-        e = launch_kbin_gather(A, lda, ta, B, ldb, tb, M, N, idx + groups[g].first, kb, GA, GB,
-                               g_stream);
+        // the group's columns of op(A) and rows of op(B), with their statistics where
+        // dgemm_run looks for them
+        const DgemmLayout L = dgemm_layout(M, N, kb, d, {true, false, false});
+        const ScaleArea sc = ws_scales(base, L.scale_off, M, N);
+        e = launch_gather_stats(A, lda, ta, B, ldb, tb, M, N, idx + groups[g].first, kb, GA, GB,
+                                sc.mb, mag_min(ws_planes(base, 0)), sc.mb + M,
+                                mag_min(ws_planes(base, L.s.bytesA)), fb ? call_st : acc_st,
+                                g_stream);
         if (e != hipSuccess) return hip_fail(e, "kbin gather");
-        rc = dgemm_run(base, {true, false}, false, false, M, N, kb, 1.0, GA, kb, GB, N,
+        rc = dgemm_run(base, {true, false, true}, false, false, M, N, kb, 1.0, GA, kb, GB, N,
                        g == 0 ? 0.0 : 1.0, T, ldt, d, fb ? call_st : acc_st, fb ? call_st : nullptr);
         if (rc) return rc;
     }
@@ -756,12 +763,12 @@ int emu_split_f64(int64_t R, int64_t Cc, const double *X, int64_t ldx, int as_b,
     F64SplitState *st = ws_states();
     const ScaleArea sc = ws_scales(s.bytesA > 0 ? s.bytesA : 1, rows, 0);
     hipError_t e = hipSuccess;
-    if (scaled) {
-        e = launch_scale_exponents(X, R, Cc, ldx, as_b != 0, sc.mb, sc.sa, g_stream);
-        if (e != hipSuccess) return hip_fail(e, "scale_exponents");
+    if (scaled && K > 0) {
+        e = launch_mag_stats(X, R, Cc, ldx, as_b != 0, sc.mb, mag_min(P), ws_status(), g_stream);
+        if (e != hipSuccess) return hip_fail(e, "mag_stats");
     }
-    const F64SplitOperand op = {X, R, Cc, ldx, as_b != 0 ? 1 : 0, scaled ? sc.sa : nullptr, P,
-                                s.RpadA, s.RliveA, st};
+    const F64SplitOperand op = {X, R, Cc, ldx, as_b != 0 ? 1 : 0, scaled ? sc.sa : nullptr, sc.mb,
+                                mag_min(P), P, s.RpadA, s.RliveA, st};
     e = launch_split_f64(&op, 1, s.KB, 6, g_split_mode, 0, ws_status(), g_stream);
     if (e != hipSuccess) return hip_fail(e, "split_f64");
     if (R > 0 && Cc > 0) {

@@ -107,7 +107,9 @@ struct F64SplitOperand {
     const double *X;
     int64_t rows, cols, ldx;    // X as stored
     int as_b;                   // packed rows are X's columns (a B operand)
-    const int *sc;              // per-packed-row weights 2^-sc (scale-aware split) or null
+    const int *sc;              // per-packed-row weights 2^-sc (scale-aware split) or null;
+                                // with it the magnitude statistics of the packed rows:
+    const unsigned long long *mx, *mn;
     uint16_t *P;                // packed planes
     int64_t Rpad;
     int64_t Rlive;              // packed rows the GEMM reads (Rpad without the row skew)
@@ -199,6 +201,19 @@ hipError_t launch_split_f64(const F64SplitOperand *ops, int nops, int64_t KB, in
 // scratch of rows (or cols) 64-bit words
 hipError_t launch_scale_exponents(const double *X, int64_t rows, int64_t cols, int64_t ldx,
                                   bool by_col, unsigned long long *mb, int *sexp, hipStream_t s);
+// per-row (by_col = 0) or per-column magnitude statistics of X: the largest
+// finite and smallest nonzero finite |x| (bit patterns; 0 and ~0 for none), and
+// ST_NAN for a non-finite entry
+hipError_t launch_mag_stats(const double *X, int64_t rows, int64_t cols, int64_t ldx, bool by_col,
+                            unsigned long long *mx, unsigned long long *mn, unsigned *status,
+                            hipStream_t s);
+// op(A)'s columns and op(B)'s rows idx[0 .. kb) into row-major M x kb and kb x N,
+// with the statistics of GA's rows and GB's columns
+hipError_t launch_gather_stats(const double *A, int64_t lda, bool ta, const double *B, int64_t ldb,
+                               bool tb, int64_t M, int64_t N, const int *idx, int64_t kb, double *GA,
+                               double *GB, unsigned long long *mxA, unsigned long long *mnA,
+                               unsigned long long *mxB, unsigned long long *mnB, unsigned *status,
+                               hipStream_t s);
 hipError_t launch_unpack(const uint16_t *P, int nc, int64_t KB, int64_t Rpad, int64_t rows,
                          int64_t cols, bool as_b, uint16_t *out, hipStream_t s);
 hipError_t launch_copy_v(const F64SplitState *st, int32_t *v, hipStream_t s);
@@ -208,17 +223,15 @@ hipError_t launch_fallback_dgemm(const unsigned *call_status, unsigned *status, 
                                  int64_t N, int64_t K, double alpha, const double *A, int64_t lda,
                                  bool ta, const double *B, int64_t ldb, bool tb, double beta,
                                  double *C, int64_t ldc, hipStream_t s);
-// K-binned scope: the class of every reduction index of op(A) op(B) (-1: left
-// out) from the ROWCOL weights sa, sb; ma, mb: K 64-bit words of scratch each.
+// K-binned scope: the reduction indices of op(A) op(B) in class order (ascending
+// inside a class; left out ones not listed) in idx and the class sizes in
+// counts[KBIN_MAX], from the ROWCOL weights sa, sb; ma, mb: K 64-bit words of
+// scratch each.
 constexpr int KBIN_WIDTH = 8, KBIN_MAX = 8;
 hipError_t launch_kbin_classes(const double *A, int64_t lda, bool ta, const double *B, int64_t ldb,
                                bool tb, int64_t M, int64_t N, int64_t K, const int *sa,
                                const int *sb, unsigned long long *ma, unsigned long long *mb,
-                               int width, int ncls, int *cls, hipStream_t s);
-// op(A)'s columns and op(B)'s rows idx[0 .. kb) into row-major M x kb and kb x N
-hipError_t launch_kbin_gather(const double *A, int64_t lda, bool ta, const double *B, int64_t ldb,
-                              bool tb, int64_t M, int64_t N, const int *idx, int64_t kb,
-                              double *GA, double *GB, hipStream_t s);
+                               int *counts, int *idx, hipStream_t s);
 // C = alpha P + beta C (the BLAS update), skipped when *skip_if is nonzero
 hipError_t launch_axpby_f64(const double *P, int64_t ldp, double *C, int64_t ldc, int64_t M,
                             int64_t N, double alpha, double beta, const unsigned *skip_if,

@@ -1,5 +1,5 @@
 // K-binned scale-aware scope (EMU_SCOPE_KBIN): classes of the reduction
-// indices and the gathers of the index groups.  An extension of the
+// indices (the gathers of the index groups are in split.hip).  An extension of the
 // scale-aware decomposition the paper names as its key next step (Sec. 9)
 // along the reduction: the products a_mk b_kn of one k share the magnitude
 // class of k, the indices of one class form a group, and every group is
@@ -23,8 +23,8 @@ __device__ inline unsigned long long mbits(double x) {
 
 // mb[k] = max over the other index of |X| 2^-w (finite entries), X stored
 // rows x cols (ldx); k runs along the columns (k_is_col) or the rows, and w is
-// indexed by the other coordinate.  One atomic maximum per k and block; mb
-// must be zero on entry.
+// indexed by the other coordinate.  With k along the columns one atomic maximum
+// per k and block, and mb must be zero on entry.
 __global__ __launch_bounds__(KT) void weighted_kmax_kernel(const double *__restrict__ X,
                                                            int64_t rows, int64_t cols, int64_t ldx,
                                                            int k_is_col, const int *__restrict__ w,
@@ -36,29 +36,37 @@ __global__ __launch_bounds__(KT) void weighted_kmax_kernel(const double *__restr
         const int64_t per = (rows + gridDim.y - 1) / gridDim.y;
         const int64_t r0 = (int64_t)blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
         double m = 0.0;
-        for (int64_t r = r0; r < r1; ++r) {
-            const double x = X[r * ldx + c];
-            if (__builtin_isfinite(x)) m = fmax(m, fabs(ldexp(x, -w[r])));
+        for (int64_t r = r0; r < r1; r += 8) {   // eight loads in flight
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = r + u < r1 ? X[(r + u) * ldx + c] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (__builtin_isfinite(x[u]))
+                    m = fmax(m, fabs(ldexp(x[u], -w[r + u < r1 ? r + u : r])));
         }
         if (m > 0.0) atomicMax(&mb[c], mbits(m));
     } else {
-        // one row per block iteration, threads along it
-        __shared__ unsigned long long red[KT / 64];
-        for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
+        // one row per wave, eight loads in flight
+        const int lane = threadIdx.x & 63;
+        for (int64_t r = (int64_t)blockIdx.x * (KT / 64) + (threadIdx.x >> 6); r < rows;
+             r += (int64_t)gridDim.x * (KT / 64)) {
             double m = 0.0;
-            for (int64_t c = threadIdx.x; c < cols; c += KT) {
-                const double x = X[r * ldx + c];
-                if (__builtin_isfinite(x)) m = fmax(m, fabs(ldexp(x, -w[c])));
+            for (int64_t c0 = lane; c0 < cols; c0 += 8 * 64) {
+                double x[8];
+                int e[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int64_t c = c0 + u * 64;
+                    x[u] = c < cols ? X[r * ldx + c] : 0.0;
+                    e[u] = c < cols ? w[c] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (__builtin_isfinite(x[u])) m = fmax(m, fabs(ldexp(x[u], -e[u])));
             }
             for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-            if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mbits(m);
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                unsigned long long b = red[0];
-                for (int i = 1; i < KT / 64; ++i) b = red[i] > b ? red[i] : b;
-                if (b) atomicMax(&mb[r], b);
-            }
-            __syncthreads();
+            if (lane == 0) mb[r] = mbits(m);
         }
     }
 }
@@ -69,19 +77,77 @@ __device__ inline int ceil_log2_d(double m) {
     return (f == 0.5) ? e - 1 : e;
 }
 
-__global__ void kclass_kernel(const unsigned long long *__restrict__ ma,
-                              const unsigned long long *__restrict__ mb, int64_t K, int width,
-                              int ncls, int *__restrict__ cls) {
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < K;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const double a = __longlong_as_double((long long)ma[k]);
-        const double b = __longlong_as_double((long long)mb[k]);
-        int c = -1;
-        if (a > 0.0 && b > 0.0) {
-            const int ne = -(ceil_log2_d(a) + ceil_log2_d(b));   // >= 0: a, b <= 1
-            c = ne / width < ncls - 1 ? ne / width : ncls - 1;
+__device__ inline int class_of(unsigned long long ma, unsigned long long mb) {
+    const double a = __longlong_as_double((long long)ma), b = __longlong_as_double((long long)mb);
+    if (!(a > 0.0 && b > 0.0)) return -1;
+    const int ne = -(ceil_log2_d(a) + ceil_log2_d(b));   // >= 0: a, b <= 1
+    return ne / KBIN_WIDTH < KBIN_MAX - 1 ? ne / KBIN_WIDTH : KBIN_MAX - 1;
+}
+
+// The index lists, by one block: each wave classes a run of indices, 64 at a
+// time (256 loads of each array in flight), counts them by ballots, and after a
+// scan over the waves puts them in their places, so every list ascends.
+constexpr int LT = 1024;
+__global__ __launch_bounds__(LT) void kbin_lists_kernel(const unsigned long long *__restrict__ ma,
+                                                        const unsigned long long *__restrict__ mb,
+                                                        int64_t K, int *__restrict__ counts,
+                                                        int *__restrict__ idx) {
+    __shared__ int at0[LT / 64][KBIN_MAX];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t per = (K + LT - 1) / LT * 64, k0 = per * w, k1 = k0 + per < K ? k0 + per : K;
+    constexpr int U = 4;
+    auto classes = [&](int64_t k, int (&c)[U]) {
+        unsigned long long a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = k + u * 64 + lane;
+            a[u] = i < k1 ? ma[i] : 0ull;
+            b[u] = i < k1 ? mb[i] : 0ull;
         }
-        cls[k] = c;
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = class_of(a[u], b[u]);
+    };
+    int n[KBIN_MAX] = {};
+    for (int64_t k = k0; k < k1; k += U * 64) {
+        int c[U];
+        classes(k, c);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < KBIN_MAX; ++i) n[i] += __popcll(__ballot(c[u] == i));
+    }
+#pragma unroll
+    for (int i = 0; i < KBIN_MAX; ++i)
+        if (lane == 0) at0[w][i] = n[i];
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int t = 0;
+        for (int i = 0; i < KBIN_MAX; ++i) {
+            const int t0 = t;
+            for (int v = 0; v < LT / 64; ++v) {
+                const int x = at0[v][i];
+                at0[v][i] = t;
+                t += x;
+            }
+            counts[i] = t - t0;
+        }
+    }
+    __syncthreads();
+    int at[KBIN_MAX];
+#pragma unroll
+    for (int i = 0; i < KBIN_MAX; ++i) at[i] = at0[w][i];
+    const unsigned long long below = (1ull << lane) - 1ull;
+    for (int64_t k = k0; k < k1; k += U * 64) {
+        int c[U];
+        classes(k, c);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < KBIN_MAX; ++i) {
+                const unsigned long long m = __ballot(c[u] == i);
+                if (c[u] == i) idx[at[i] + __popcll(m & below)] = (int)(k + u * 64 + lane);
+                at[i] += __popcll(m);
+            }
     }
 }
 
@@ -89,28 +155,6 @@ __global__ void fill_u64_zero_kernel(unsigned long long *p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0ull;
-}
-
-// Columns idx[0 .. kb) of op(A) (A stored M x K, or K x M when ta) into a
-// row-major M x kb matrix G.
-__global__ void gather_opa_kernel(const double *__restrict__ A, int64_t lda, int ta, int64_t M,
-                                  const int *__restrict__ idx, int64_t kb, double *__restrict__ G) {
-    for (int64_t m = blockIdx.x; m < M; m += gridDim.x)
-        for (int64_t j = threadIdx.x; j < kb; j += blockDim.x) {
-            const int64_t k = idx[j];
-            G[m * kb + j] = ta ? A[k * lda + m] : A[m * lda + k];
-        }
-}
-
-// Rows idx[0 .. kb) of op(B) (B stored K x N, or N x K when tb) into a
-// row-major kb x N matrix G.
-__global__ void gather_opb_kernel(const double *__restrict__ B, int64_t ldb, int tb, int64_t N,
-                                  const int *__restrict__ idx, int64_t kb, double *__restrict__ G) {
-    for (int64_t j = blockIdx.x; j < kb; j += gridDim.x) {
-        const int64_t k = idx[j];
-        for (int64_t n = threadIdx.x; n < N; n += blockDim.x)
-            G[j * N + n] = tb ? B[n * ldb + k] : B[k * ldb + n];
-    }
 }
 
 // C = fl(fl(alpha P) + fl(beta C)) (fl(alpha P) when beta == 0), unless the
@@ -134,22 +178,23 @@ int grid_rows(int64_t n) { return (int)(n < 4096 ? (n > 0 ? n : 1) : 4096); }
 hipError_t launch_kbin_classes(const double *A, int64_t lda, bool ta, const double *B, int64_t ldb,
                                bool tb, int64_t M, int64_t N, int64_t K, const int *sa,
                                const int *sb, unsigned long long *ma, unsigned long long *mb,
-                               int width, int ncls, int *cls, hipStream_t s) {
-    const int fg = (int)((2 * K + 255) / 256 < 1024 ? (2 * K + 255) / 256 : 1024);
-    fill_u64_zero_kernel<<<fg, 256, 0, s>>>(ma, K);
-    fill_u64_zero_kernel<<<fg, 256, 0, s>>>(mb, K);
+                               int *counts, int *idx, hipStream_t s) {
+    const int fg = (int)((K + 255) / 256 < 1024 ? (K + 255) / 256 : 1024);
+    if (!ta) fill_u64_zero_kernel<<<fg, 256, 0, s>>>(ma, K);
+    if (tb) fill_u64_zero_kernel<<<fg, 256, 0, s>>>(mb, K);
     // op(A): k along A's columns (stored M x K) or rows (stored K x M); weights sa by m
     auto launch = [&](const double *X, int64_t rows, int64_t cols, int64_t ld, bool k_is_col,
                       const int *w, unsigned long long *out) {
         if (k_is_col) {
             const int64_t gx = (cols + KT - 1) / KT;
-            int64_t gy = (rows + 255) / 256;
+            int64_t gy = (rows + 63) / 64;      // 256 rows a slice: 118 us at 1024 x 16384
             if (gy > 65535) gy = 65535;
             if (gx * gy > 16384) gy = 16384 / gx > 1 ? 16384 / gx : 1;
             weighted_kmax_kernel<<<dim3((unsigned)gx, (unsigned)gy), KT, 0, s>>>(X, rows, cols, ld,
                                                                                   1, w, out);
         } else {
-            weighted_kmax_kernel<<<grid_rows(rows), KT, 0, s>>>(X, rows, cols, ld, 0, w, out);
+            weighted_kmax_kernel<<<grid_rows((rows + KT / 64 - 1) / (KT / 64)), KT, 0, s>>>(
+                X, rows, cols, ld, 0, w, out);
         }
     };
     if (ta) launch(A, K, M, lda, false, sa, ma);
@@ -157,15 +202,7 @@ hipError_t launch_kbin_classes(const double *A, int64_t lda, bool ta, const doub
     // op(B): k along B's rows (stored K x N) or columns (stored N x K); weights sb by n
     if (tb) launch(B, N, K, ldb, true, sb, mb);
     else launch(B, K, N, ldb, false, sb, mb);
-    kclass_kernel<<<fg, 256, 0, s>>>(ma, mb, K, width, ncls, cls);
-    return hipGetLastError();
-}
-
-hipError_t launch_kbin_gather(const double *A, int64_t lda, bool ta, const double *B, int64_t ldb,
-                              bool tb, int64_t M, int64_t N, const int *idx, int64_t kb,
-                              double *GA, double *GB, hipStream_t s) {
-    gather_opa_kernel<<<grid_rows(M), 256, 0, s>>>(A, lda, ta ? 1 : 0, M, idx, kb, GA);
-    gather_opb_kernel<<<grid_rows(kb), 256, 0, s>>>(B, ldb, tb ? 1 : 0, N, idx, kb, GB);
+    kbin_lists_kernel<<<1, LT, 0, s>>>(ma, mb, K, counts, idx);
     return hipGetLastError();
 }
 

@@ -182,9 +182,8 @@ __device__ inline double wave_max(double m) {
 // max |x| over an operand (level-0 maximum) and the input-domain checks of
 // Eq. (bf16rangefp64).  A wave reads 512 consecutive entries of a row (eight
 // loads of 512 bytes in flight); a matrix without gaps between its rows is
-// read as one row.  With weights (sc non-null) the operand is read as
-// x 2^-sc[p], p the packed row of x (X's row, or X's column for a B operand),
-// and the checks apply to it.  Bound by HBM: 5.9 TB/s at 8192^2.
+// read as one row.  Bound by HBM: 5.9 TB/s at 8192^2.  (Operands with weights
+// take f64_weights_kernel instead.)
 __global__ __launch_bounds__(MAX_THREADS) void f64_maxabs_kernel(F64SplitArgs a) {
     __shared__ double red[MAX_THREADS / 64];
     int b, nb;
@@ -196,7 +195,7 @@ __global__ __launch_bounds__(MAX_THREADS) void f64_maxabs_kernel(F64SplitArgs a)
     double m = 0.0;
     bool nonfinite = false, range = false;
     const double lo = 0x1p-126, hi = 0x1.fep127;   // (2 - 2^-7) 2^127
-    const bool one_row = op.sc == nullptr && op.ldx == op.cols;
+    const bool one_row = op.ldx == op.cols;
     const int64_t rows = one_row ? 1 : op.rows;
     const int64_t cols = one_row ? op.rows * op.cols : op.cols;
     constexpr int U = 8;
@@ -215,13 +214,6 @@ __global__ __launch_bounds__(MAX_THREADS) void f64_maxabs_kernel(F64SplitArgs a)
         } else {
 #pragma unroll
             for (int u = 0; u < U; ++u) x[u] = c0 + u * 64 < cols ? row[c0 + u * 64] : 0.0;
-        }
-        if (op.sc) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t c = c0 + u * 64;
-                if (c < cols) x[u] = ldexp(x[u], -op.sc[op.as_b ? c : r]);
-            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -724,9 +716,14 @@ __global__ __launch_bounds__(SPLIT_THREADS) void row_maxbits_kernel(
     __shared__ unsigned long long red[SPLIT_THREADS / 64];
     for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
         double m = 0.0;
-        for (int64_t c = threadIdx.x; c < cols; c += SPLIT_THREADS) {
-            const double x = X[r * ldx + c];
-            if (__builtin_isfinite(x)) m = fmax(m, fabs(x));
+        for (int64_t c0 = threadIdx.x; c0 < cols; c0 += 8 * SPLIT_THREADS) {   // eight loads in flight
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                x[u] = c0 + u * SPLIT_THREADS < cols ? X[r * ldx + c0 + u * SPLIT_THREADS] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (__builtin_isfinite(x[u])) m = fmax(m, fabs(x[u]));
         }
         for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dbits(m);
@@ -753,9 +750,16 @@ __global__ __launch_bounds__(SPLIT_THREADS) void col_maxbits_kernel(
     const int64_t r0 = (int64_t)blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
     double m = 0.0;
     if (c < cols)
-        for (int64_t r = r0 + w; r < r1; r += SPLIT_THREADS / 64) {
-            const double x = X[r * ldx + c];
-            if (__builtin_isfinite(x)) m = fmax(m, fabs(x));
+        for (int64_t r = r0 + w; r < r1; r += 8 * (SPLIT_THREADS / 64)) {   // eight loads in flight
+            double x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int64_t ru = r + u * (SPLIT_THREADS / 64);
+                x[u] = ru < r1 ? X[ru * ldx + c] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (__builtin_isfinite(x[u])) m = fmax(m, fabs(x[u]));
         }
     red[w][lane] = dbits(m);
     __syncthreads();
@@ -779,6 +783,177 @@ __global__ void fill_u64_kernel(unsigned long long *p, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0ull;
+}
+
+// Magnitude statistics for the scale-aware split: per row or column the largest
+// finite and the smallest nonzero finite magnitude (bit patterns; 0 and ~0 for
+// none), and the NaN/infinity flag.  They give the weights, the level-0 maximum of
+// the scaled operand and its domain checks without reading it a second time.
+struct MagStat {
+    unsigned long long mx = 0ull, mn = ~0ull;
+    bool nonfinite = false;
+    __device__ void add(double x) {
+        const unsigned long long a = dbits(fabs(x));
+        if (!__builtin_isfinite(x)) { nonfinite = true; return; }
+        mx = a > mx ? a : mx;
+        mn = (a != 0ull && a < mn) ? a : mn;
+    }
+};
+
+// block-wide result of one row, valid in thread 0
+__device__ inline void block_magstat(MagStat &s, unsigned long long (*red)[2]) {
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long a = __shfl_xor(s.mx, off), b = __shfl_xor(s.mn, off);
+        s.mx = a > s.mx ? a : s.mx;
+        s.mn = b < s.mn ? b : s.mn;
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6][0] = s.mx;
+        red[threadIdx.x >> 6][1] = s.mn;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int i = 1; i < SPLIT_THREADS / 64; ++i) {
+            s.mx = red[i][0] > s.mx ? red[i][0] : s.mx;
+            s.mn = red[i][1] < s.mn ? red[i][1] : s.mn;
+        }
+    __syncthreads();
+}
+
+// one block per row, four loads in flight per thread.  IDX: the row's entries are
+// those of the columns idx[0 .. cols), and they are written to G as well.
+template <bool IDX>
+__global__ __launch_bounds__(SPLIT_THREADS) void row_stats_kernel(
+    const double *__restrict__ X, int64_t rows, int64_t cols, int64_t ldx, int64_t cstride,
+    const int *__restrict__ idx, double *__restrict__ G, unsigned long long *__restrict__ mx,
+    unsigned long long *__restrict__ mn, unsigned *__restrict__ status) {
+    __shared__ unsigned long long red[SPLIT_THREADS / 64][2];
+    bool nonfinite = false;
+    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
+        const double *row = X + r * ldx;
+        MagStat s;
+        for (int64_t c0 = threadIdx.x; c0 < cols; c0 += 4 * SPLIT_THREADS) {
+            double x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t c = c0 + u * SPLIT_THREADS;
+                x[u] = c < cols ? row[IDX ? idx[c] * cstride : c] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t c = c0 + u * SPLIT_THREADS;
+                s.add(x[u]);
+                if (IDX && c < cols) G[r * cols + c] = x[u];
+            }
+        }
+        nonfinite |= s.nonfinite;
+        block_magstat(s, red);
+        if (threadIdx.x == 0) {
+            mx[r] = s.mx;
+            mn[r] = s.mn;
+        }
+    }
+    if (__any(nonfinite) && (threadIdx.x & 63) == 0) atomicOr(status, ST_NAN);
+}
+
+// 64 columns per block and a slice of the rows per blockIdx.y; lanes run along
+// the columns, the four waves over rows, four loads in flight; two atomics per
+// column and block.  mx and mn must be 0 and ~0 on entry.  IDX: the rows are
+// idx[0 .. rows), and they are written to G as well.
+template <bool IDX>
+__global__ __launch_bounds__(SPLIT_THREADS) void col_stats_kernel(
+    const double *__restrict__ X, int64_t rows, int64_t cols, int64_t ldx, int64_t cstride,
+    const int *__restrict__ idx, double *__restrict__ G, unsigned long long *__restrict__ mx,
+    unsigned long long *__restrict__ mn, unsigned *__restrict__ status) {
+    __shared__ unsigned long long red[SPLIT_THREADS / 64][64][2];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t per = (rows + gridDim.y - 1) / gridDim.y;
+    const int64_t r0 = (int64_t)blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
+    MagStat s;
+    if (c < cols)
+        for (int64_t r = r0 + w; r < r1; r += 4 * (SPLIT_THREADS / 64)) {
+            double x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t ru = r + u * (SPLIT_THREADS / 64);
+                x[u] = ru < r1 ? X[(IDX ? idx[ru] : ru) * ldx + c * cstride] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int64_t ru = r + u * (SPLIT_THREADS / 64);
+                s.add(x[u]);
+                if (IDX && ru < r1) G[ru * cols + c] = x[u];
+            }
+        }
+    red[w][lane][0] = s.mx;
+    red[w][lane][1] = s.mn;
+    if (__any(s.nonfinite) && lane == 0) atomicOr(status, ST_NAN);
+    __syncthreads();
+    if (w == 0 && c < cols) {
+        for (int i = 1; i < SPLIT_THREADS / 64; ++i) {
+            s.mx = red[i][lane][0] > s.mx ? red[i][lane][0] : s.mx;
+            s.mn = red[i][lane][1] < s.mn ? red[i][lane][1] : s.mn;
+        }
+        if (s.mx) atomicMax(&mx[c], s.mx);
+        if (s.mn != ~0ull) atomicMin(&mn[c], s.mn);
+    }
+}
+
+__global__ void stats_init_kernel(unsigned long long *mx, unsigned long long *mn, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        mx[i] = 0ull;
+        mn[i] = ~0ull;
+    }
+}
+
+// From the statistics of an operand's packed rows: their weights, and in place of
+// f64_maxabs_kernel the level-0 maximum of the scaled operand, its range check
+// and the cleared state.  A scaled magnitude is at most 1, so only entries below
+// 2^-126 leave the range.  Where the smallest one underflows to an exact zero
+// (which is in the domain), the row's entries are looked through for others.
+__global__ __launch_bounds__(SPLIT_THREADS) void f64_weights_kernel(F64SplitArgs a) {
+    __shared__ double red[SPLIT_THREADS / 64];
+    int b, nb;
+    const F64SplitOperand &op = operand_of_block(a, b, nb);
+    if (b == 0) {
+        unsigned *w = reinterpret_cast<unsigned *>(op.st);
+        for (int i = threadIdx.x; i < (int)(sizeof(F64SplitState) / 4); i += SPLIT_THREADS) w[i] = 0u;
+    }
+    const int64_t n = op.as_b ? op.cols : op.rows, len = op.as_b ? op.rows : op.cols;
+    const double lo = 0x1p-126;
+    double m = 0.0;
+    bool range = false;
+    for (int64_t p = (int64_t)b * SPLIT_THREADS + threadIdx.x; p < n; p += (int64_t)nb * SPLIT_THREADS) {
+        const double mx = __longlong_as_double((long long)op.mx[p]);
+        const int s = mx > 0.0 ? ceil_log2_pos(mx) : 0;
+        const_cast<int *>(op.sc)[p] = s;
+        m = fmax(m, ldexp(mx, -s));
+        if (mx > 0.0) {
+            const double t = ldexp(__longlong_as_double((long long)op.mn[p]), -s);
+            if (t > 0.0) {
+                range |= t < lo;
+            } else {
+                for (int64_t i = 0; i < len && !range; ++i) {
+                    const double x = op.X[op.as_b ? i * op.ldx + p : p * op.ldx + i];
+                    const double y = fabs(ldexp(x, -s));
+                    range = y > 0.0 && y < lo;
+                }
+            }
+        }
+    }
+    m = wave_max(m);
+    const unsigned flags = block_or(range ? ST_RANGE : 0u);
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = m;
+        if (flags) atomicOr(a.status, flags);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < SPLIT_THREADS / 64; ++i) m = fmax(m, red[i]);
+        partial_max(op, a.KB, 0)[b] = m;
+    }
 }
 
 // Test hook: packed planes back to plain row-major planes in X's orientation.
@@ -892,13 +1067,23 @@ hipError_t launch_split_f64(const F64SplitOperand *ops, int nops, int64_t KB, in
     auto clamp = [](int64_t n, int hi) { return (int)(n < 1 ? 1 : n < hi ? n : hi); };
     // one 512-entry segment of a row per wave, at most MAX_BLOCKS blocks per operand
     auto max_blocks = [&](const F64SplitOperand &o) {
-        const int64_t segs = o.sc == nullptr && o.ldx == o.cols ? (o.rows * o.cols + 511) / 512
+        const int64_t segs = o.ldx == o.cols ? (o.rows * o.cols + 511) / 512
                                                                 : o.rows * ((o.cols + 511) / 512);
         return clamp((segs + MAX_THREADS / 64 - 1) / (MAX_THREADS / 64), MAX_BLOCKS);
     };
-    a.blocks0 = a.max0 = max_blocks(ops[0]);
-    a.blocks1 = a.max1 = nops > 1 ? max_blocks(ops[1]) : 0;
-    f64_maxabs_kernel<<<a.blocks0 + a.blocks1, MAX_THREADS, 0, s>>>(a);
+    if (ops[0].sc != nullptr) {
+        // scale-aware: weights and maxima from the operands' statistics
+        auto row_blocks = [&](const F64SplitOperand &o) {
+            return clamp(((o.as_b ? o.cols : o.rows) + SPLIT_THREADS - 1) / SPLIT_THREADS, MAX_BLOCKS);
+        };
+        a.blocks0 = a.max0 = row_blocks(ops[0]);
+        a.blocks1 = a.max1 = nops > 1 ? row_blocks(ops[1]) : 0;
+        f64_weights_kernel<<<a.blocks0 + a.blocks1, SPLIT_THREADS, 0, s>>>(a);
+    } else {
+        a.blocks0 = a.max0 = max_blocks(ops[0]);
+        a.blocks1 = a.max1 = nops > 1 ? max_blocks(ops[1]) : 0;
+        f64_maxabs_kernel<<<a.blocks0 + a.blocks1, MAX_THREADS, 0, s>>>(a);
+    }
     // one 64-row x 32-index item per block, at most SPLIT_BLOCKS blocks per operand
     a.blocks0 = clamp(KB * (ops[0].Rlive / ROWS_PER_BLOCK), SPLIT_BLOCKS);
     a.blocks1 = nops > 1 ? clamp(KB * (ops[1].Rlive / ROWS_PER_BLOCK), SPLIT_BLOCKS) : 0;
@@ -944,6 +1129,54 @@ hipError_t launch_scale_exponents(const double *X, int64_t rows, int64_t cols, i
         row_maxbits_kernel<<<g, SPLIT_THREADS, 0, s>>>(X, rows, cols, ldx, mb);
     }
     maxbits_to_exponent_kernel<<<fg, 256, 0, s>>>(mb, n, sexp);
+    return hipGetLastError();
+}
+
+namespace {
+// grid of a pass over columns: 64 per block, about 64 rows per slice (with 256 a
+// 161-row group of 1024 columns took 21 us on 16 blocks)
+dim3 col_grid(int64_t rows, int64_t cols) {
+    const int64_t gx = (cols + 63) / 64;
+    int64_t gy = (rows + 63) / 64;
+    if (gy > 65535) gy = 65535;
+    if (gx * gy > 8192) gy = 8192 / gx > 1 ? 8192 / gx : 1;
+    return dim3((unsigned)gx, (unsigned)(gy > 0 ? gy : 1));
+}
+int row_grid(int64_t rows) { return (int)(rows < 8192 ? (rows > 0 ? rows : 1) : 8192); }
+hipError_t stats_init(unsigned long long *mx, unsigned long long *mn, int64_t n, hipStream_t s) {
+    stats_init_kernel<<<(int)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024), 256, 0, s>>>(mx, mn, n);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_mag_stats(const double *X, int64_t rows, int64_t cols, int64_t ldx, bool by_col,
+                            unsigned long long *mx, unsigned long long *mn, unsigned *status,
+                            hipStream_t s) {
+    const int64_t n = by_col ? cols : rows;
+    if (n == 0) return hipSuccess;
+    if (by_col) {
+        hipError_t e = stats_init(mx, mn, n, s);
+        if (e != hipSuccess) return e;
+        col_stats_kernel<false><<<col_grid(rows, cols), SPLIT_THREADS, 0, s>>>(
+            X, rows, cols, ldx, 1, nullptr, nullptr, mx, mn, status);
+    } else {
+        row_stats_kernel<false><<<row_grid(rows), SPLIT_THREADS, 0, s>>>(
+            X, rows, cols, ldx, 1, nullptr, nullptr, mx, mn, status);
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_gather_stats(const double *A, int64_t lda, bool ta, const double *B, int64_t ldb,
+                               bool tb, int64_t M, int64_t N, const int *idx, int64_t kb, double *GA,
+                               double *GB, unsigned long long *mxA, unsigned long long *mnA,
+                               unsigned long long *mxB, unsigned long long *mnB, unsigned *status,
+                               hipStream_t s) {
+    hipError_t e = stats_init(mxB, mnB, N, s);
+    if (e != hipSuccess) return e;
+    row_stats_kernel<true><<<row_grid(M), SPLIT_THREADS, 0, s>>>(
+        A, M, kb, ta ? 1 : lda, ta ? lda : 1, idx, GA, mxA, mnA, status);
+    col_stats_kernel<true><<<col_grid(kb, N), SPLIT_THREADS, 0, s>>>(
+        B, kb, N, tb ? 1 : ldb, tb ? ldb : 1, idx, GB, mxB, mnB, status);
     return hipGetLastError();
 }
 
