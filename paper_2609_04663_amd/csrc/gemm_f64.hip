@@ -99,6 +99,11 @@ hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, in
                 return launch_w<3, 4, false, 2>(a, s);
             return launch_s<3, 2, 3, false>(a, s);
         case 4:
+            // 32 x 64 tiles where they number no more than the CUs (nprod 10 calls,
+            // 64 x 64 / 32 x 64, us: 512^3 27.1 / 24.3, 700 x 600 x 800 37.2 / 32.8,
+            // 300 x 300 x 1000 37.4 / 32.0; 1024^3, 512 tiles, 48.0 / 53.7)
+            if (few_tiles(32) || ((M + 31) / 32) * ((N + DGEMM_NT - 1) / DGEMM_NT) == pw)
+                return launch_w<4, 4, false, 1, false>(a, s);
             if (long_k)
                 return launch_w<4, 4, false, 2, false>(a, s);
             return launch_s<4, 1, 3, false>(a, s);

@@ -34,7 +34,7 @@ struct CfgW {
     static_assert(BMW == 1 || BMW == 2 || BMW == 4, "wave tile");
     static_assert(4 * COPIES * 1024 == STAGE && 4 * A_COPIES * 1024 == NPL * A_BYTES,
                   "copy split");
-    static_assert(BMW != 1 || NPL == 6, "one-block tiles copy six planes");
+    static_assert(BMW != 1 || NPL % 2 == 0, "one-block tiles copy planes in pairs");
     static_assert(NS * STAGE + ACC64_BYTES <= 160 * 1024, "LDS");
 };
 
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256, 1) void gemm_f64w_kernel(
 
     // Copy c of a k-block by wave w moves 1 KB part g = 4 c + w of the list
     // A parts (plane-major, 2 BMW parts a plane), then B parts: for BMW = 1,
-    // c < 3 moves part (w & 1) of A plane 2 c + (w >> 1); for BMW >= 2,
+    // c < A_COPIES moves part (w & 1) of A plane 2 c + (w >> 1); for BMW >= 2,
     // c < A_COPIES moves part 4 (c % (BMW / 2)) + w of A plane c / (BMW / 2);
     // the rest move part w of B plane c - A_COPIES.
     // ak, bk: the k-block's slab of plane 0 at the copied tile's first row.
@@ -310,6 +310,7 @@ template hipError_t launch_w<1, 4, false, 4, false>(const DgemmArgs &, hipStream
 template hipError_t launch_w<2, 4, false, 2>(const DgemmArgs &, hipStream_t);
 template hipError_t launch_w<3, 4, false, 2>(const DgemmArgs &, hipStream_t);
 template hipError_t launch_w<4, 4, false, 2, false>(const DgemmArgs &, hipStream_t);
+template hipError_t launch_w<4, 4, false, 1, false>(const DgemmArgs &, hipStream_t);
 template hipError_t launch_w<5, 3, true, 2, false>(const DgemmArgs &, hipStream_t);
 template hipError_t launch_w<6, 4, false>(const DgemmArgs &, hipStream_t);
 template hipError_t launch_w<7, 3, false>(const DgemmArgs &, hipStream_t);
