@@ -646,7 +646,7 @@ int sgemm_tile_m(int64_t M, int64_t N, int64_t KB) {
         if (t == 64) {
             const int64_t rem = wg % (2 * cus);
             us = (double)(wg / (2 * cus)) * 0.58;
-            if (rem > 0) us += 0.33 + (rem > cus ? 0.25 * (double)(rem - cus) / (double)cus : 0.0);
+            if (rem > 0) us += rem > cus ? 0.58 : 0.33;
             us *= kb;
         } else {
             us = (double)((wg + cus - 1) / cus) * kb * (t == 192 ? 1.13 : 0.80) + (t == 192 ? 6.0 : 4.0);
