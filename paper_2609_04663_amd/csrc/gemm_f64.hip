@@ -15,9 +15,9 @@
 // Three kernels.  gemm_f64_kernel (gemm_f64s.hip): 32 x 32 x 16 MFMA, 4 waves in a 2 x 2
 // grid; wave tile (32 BM) x 32, output tile (64 BM) x 64.  gemm_f64w_kernel
 // (gemm_f64w.hip): 16 x 16 x 32 MFMA on a (16 BMW) x 32 wave tile, one barrier
-// per k-block; it runs depths d >= 6 (BMW = 1) and, with BMW = 2 or 4, the
-// long reductions of d = 1, 2, 4, 5 and the small grids of d = 1 .. 3 (the
-// choice is made in launch_gemm_f64).  Per k-block of 32 the d planes of both operands are copied
+// per k-block; it runs depths d >= 7 and small grids.  gemm_f64t_kernel
+// (gemm_f64t.hip): 32 x 32 x 16 MFMA over whole panels, d = 3 .. 6 on grids that
+// fill the CUs.  (The choice is made in launch_gemm_f64.)  Per k-block of 32 the d planes of both operands are copied
 // straight into LDS (global_load_lds_dwordx4) through a ring of LDS stages.
 // Each wave keeps one FP32 accumulator set per product for the whole panel
 // (all N_p live, so every fragment read from LDS feeds every product that
@@ -59,14 +59,13 @@ hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, in
                            int64_t N, int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
                            const int *sa, const int *sb, double alpha, double beta, int d,
                            const unsigned *skip_if, hipStream_t s) {
-    // Depths 1 .. 5 take the wide kernel's 64 x 64 tiles (BMW = 2) where it
-    // measured faster than the 32 x 32 x 16 kernel: long reductions (K > 1024)
-    // of d = 2, 4 and 5 (8, 2 and 5 % at 8192^3), and grids of d = 1 .. 3
-    // whose 128- or 256-row tiles would number fewer than the CUs (1.5 - 1.9x
-    // at 1000 x 1000 x 8200).  The other long reductions of d = 1 take its
-    // 128 x 64 tiles (BMW = 4; 7-40 % faster).  Short reductions of d = 1, 2,
-    // 4, 5 and the large grids of d = 3 measured faster on the 32 x 32 x 16
-    // kernel.  Both kernels give the same bits.
+    // First gemm_f64t_kernel where use_t64 says so.  The other calls of depths
+    // 1 .. 5 take the wide kernel's 64 x 64 tiles (BMW = 2) where it measured
+    // faster than the 32 x 32 x 16 kernel: long reductions (K > 1024) of d = 2,
+    // 4 and 5 (8, 2 and 5 % at 8192^3), and grids of d = 1 .. 3 whose 128- or
+    // 256-row tiles would number fewer than the CUs (1.5 - 1.9x at 1000 x 1000
+    // x 8200).  The other long reductions of d = 1 take its 128 x 64 tiles (BMW
+    // = 4; 7-40 % faster).  All kernels give the same bits.
     const DgemmArgs a = {Ap, Bp, C, M, N, KB, RpadA, RpadB, ldc, sa, sb, alpha, beta,
                          skip_if};
     const int pw = persistent_workgroups();

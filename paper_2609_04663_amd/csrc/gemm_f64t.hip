@@ -1,4 +1,5 @@
-// Long reductions of depths d = 3 .. 6 on the 32 x 32 x 16 MFMA with wave tiles
+// Emulated DGEMM, depths d = 3 .. 6 over whole panels (see gemm_f64.hip for the
+// method and the choice): 32 x 32 x 16 MFMA with wave tiles
 // of BM 32 x 32 blocks: four waves in a 2 x 2 grid, output tile (64 BM) x 64
 // (d = 6 and 5: BM = 1; d = 4 and 3: BM = 2).  Every retained product's
 // accumulators (16 registers per block) stay live for the whole panel: the
