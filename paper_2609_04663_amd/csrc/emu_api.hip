@@ -143,13 +143,11 @@ unsigned *ws_status() { return ws_status(g_ws.base); }
 F64SplitState *ws_states() { return ws_states(g_ws.base); }
 uint16_t *ws_planes(size_t off) { return ws_planes(g_ws.base, off); }
 
-// Scale-aware split scratch after the planes (256-byte aligned): 64-bit maxima
-// for the nA rows of A and the nB columns of B, then their int32 exponents.
+// Scale-aware split scratch after the planes (256-byte aligned).
 struct ScaleArea {
     unsigned long long *mb;   // [nA + nB]
     int *sa, *sb;             // [nA], [nB]
 };
-size_t scale_bytes(int64_t nA, int64_t nB) { return 256 + (size_t)(nA + nB) * 12; }
 ScaleArea ws_scales(char *base, size_t planes_bytes, int64_t nA, int64_t nB) {
     const size_t off = (HDR + planes_bytes + 255) / 256 * 256;
     ScaleArea a;
@@ -230,26 +228,6 @@ int check_gemm_args(bool ta, bool tb, int64_t M, int64_t N, int64_t K, const voi
     if (M > (int64_t)1 << 31 || N > (int64_t)1 << 31 || K > (int64_t)1 << 36)
         return fail(EMU_EINVAL, "matrix dimension too large");
     return EMU_OK;
-}
-
-struct Shape {
-    int64_t KB, RpadA, RpadB, RliveA, RliveB;
-    size_t bytesA, bytesB;
-};
-
-// Packed sizes: rows padded to whole GEMM tiles (tile_m, tile_n are multiples
-// of ROW_GROUP), reduction padded to whole k-blocks.
-Shape plan(int64_t M, int64_t N, int64_t K, int nplanes, int64_t tile_m, int64_t tile_n,
-           int64_t KB = 0) {
-    Shape s;
-    s.KB = KB > 0 ? KB : (K + KBLK - 1) / KBLK;
-    s.RliveA = round_up(M, tile_m);
-    s.RliveB = round_up(N, tile_n);
-    s.RpadA = s.RliveA + ROW_SKEW_TILES * tile_m;
-    s.RpadB = s.RliveB + ROW_SKEW_TILES * tile_n;
-    s.bytesA = (size_t)nplanes * plane_elems(s.KB, s.RpadA) * 2;
-    s.bytesB = (size_t)nplanes * plane_elems(s.KB, s.RpadB) * 2;
-    return s;
 }
 
 }  // namespace
@@ -463,25 +441,6 @@ DgemmOpts current_opts() {
     return {g_split_scope != EMU_SCOPE_OPERAND, g_fallback == EMU_FALLBACK_FP64, false};
 }
 
-// Workspace areas of one emulated DGEMM after the header: packed planes, then
-// (256-byte aligned) the weights of the scale-aware split.
-struct DgemmLayout {
-    Shape s;
-    size_t scale_off, bytes;
-};
-
-DgemmLayout dgemm_layout(int64_t M, int64_t N, int64_t K, int d, DgemmOpts o) {
-    DgemmLayout L;
-    // the DGEMM kernel's tile rows and k-block multiple (padding is zero)
-    const int64_t KB = (K + KBLK - 1) / KBLK;
-    L.s = plan(M, N, K, dgemm_planes(d), dgemm_tile_rows(d, M, N, KB), DGEMM_NT,
-               dgemm_kb_padded(d, M, N, KB));
-    auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    L.scale_off = up(L.s.bytesA + L.s.bytesB);
-    L.bytes = up(L.scale_off + (o.scaled ? scale_bytes(M, N) : 0));
-    return L;
-}
-
 // The smallest magnitudes of an operand's packed rows (8 bytes of the 64 that
 // plane 0 has for each row of a k-block), until the split writes the planes.
 unsigned long long *mag_min(uint16_t *planes) {
@@ -492,19 +451,18 @@ unsigned long long *mag_min(uint16_t *planes) {
 // the current call (offset 64) that an armed fallback reads.
 unsigned *ws_call_status(char *base) { return reinterpret_cast<unsigned *>(base + 64); }
 
-// The emulated DGEMM on a workspace at base (header, planes, weights), after
+// The emulated DGEMM on a workspace at base (header, then the areas of L), after
 // argument validation; M, N, K > 0 and alpha != 0.  status_to: the word the
 // split's flags go to when the fallback is not armed (null: the accumulated
 // word).  skip_if: the word of a fallback armed by the caller, which makes the
 // product GEMM unneeded once it is nonzero (its own word where o.fallback).
-int dgemm_run(char *base, DgemmOpts o, bool ta, bool tb, int64_t M, int64_t N, int64_t K,
+int dgemm_run(char *base, const DgemmLayout &L, DgemmOpts o, bool ta, bool tb, int64_t M, int64_t N, int64_t K,
               double alpha, const double *A, int64_t lda, const double *B, int64_t ldb,
               double beta, double *C, int64_t ldc, int d, unsigned *status_to = nullptr,
               const unsigned *skip_if = nullptr) {
     // Only the slices the retained products read are materialised; the levels
     // after them never influence the earlier slices.
     const int np = dgemm_planes(d);
-    const DgemmLayout L = dgemm_layout(M, N, K, d, o);
     const Shape &s = L.s;
     uint16_t *Ap = ws_planes(base, 0), *Bp = ws_planes(base, s.bytesA);
     F64SplitState *st = ws_states(base);
@@ -546,7 +504,7 @@ int dgemm_run(char *base, DgemmOpts o, bool ta, bool tb, int64_t M, int64_t N, i
     // C, the product GEMM leaves it alone (so beta C is still there to read)
     e = launch_gemm_f64(Ap, Bp, C, M, N, s.KB, s.RpadA, s.RpadB, ldc, o.scaled ? sc.sa : nullptr,
                         o.scaled ? sc.sb : nullptr, alpha, beta, d,
-                        o.fallback ? split_status : skip_if, g_stream);
+                        L.panels, o.fallback ? split_status : skip_if, g_stream);
     if (e != hipSuccess) return hip_fail(e, "gemm_f64");
     if (o.fallback) {
         e = launch_fallback_dgemm(split_status, ws_status(base), M, N, K, alpha, A, lda, ta, B, ldb,
@@ -571,8 +529,9 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
     const bool fb = g_fallback == EMU_FALLBACK_FP64;
     const bool direct = alpha == 1.0 && beta == 0.0;
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
-    // workspace after the area of the largest group's DGEMM (its planes and weights)
-    size_t off = up(dgemm_layout(M, N, K, d, {true, false, false}).bytes);
+    // workspace after the area that the groups' DGEMMs share (planes and weights)
+    const size_t area = dgemm_layout(d, M, N, K, true, device_cu_count()).bytes;
+    size_t off = up(area);
     const int64_t MN = M > N ? M : N;
     const size_t o_sa = off;  off = up(off + (size_t)M * 4);
     const size_t o_sb = off;  off = up(off + (size_t)N * 4);
@@ -627,14 +586,14 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
         const int64_t kb = groups[g].second;
         // the group's columns of op(A) and rows of op(B), with their statistics where
         // dgemm_run looks for them
-        const DgemmLayout L = dgemm_layout(M, N, kb, d, {true, false, false});
+        const DgemmLayout L = kbin_group_layout(d, M, N, kb, device_cu_count(), area);
         const ScaleArea sc = ws_scales(base, L.scale_off, M, N);
         e = launch_gather_stats(A, lda, ta, B, ldb, tb, M, N, idx + groups[g].first, kb, GA, GB,
                                 sc.mb, mag_min(ws_planes(base, 0)), sc.mb + M,
                                 mag_min(ws_planes(base, L.s.bytesA)), fb ? call_st : acc_st,
                                 g_stream);
         if (e != hipSuccess) return hip_fail(e, "kbin gather");
-        rc = dgemm_run(base, {true, false, true}, false, false, M, N, kb, 1.0, GA, kb, GB, N,
+        rc = dgemm_run(base, L, {true, false, true}, false, false, M, N, kb, 1.0, GA, kb, GB, N,
                        g == 0 ? 0.0 : 1.0, T, ldt, d, fb ? call_st : acc_st, fb ? call_st : nullptr);
         if (rc) return rc;
     }
@@ -690,9 +649,10 @@ int emu_dgemm_ex(char transa, char transb, int64_t M, int64_t N, int64_t K, doub
     if (g_split_scope == EMU_SCOPE_KBIN)
         return dgemm_kbin(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, d);
     const DgemmOpts o = current_opts();
-    rc = ensure_workspace(dgemm_layout(M, N, K, d, o).bytes);
+    const DgemmLayout L = dgemm_layout(d, M, N, K, o.scaled, device_cu_count());
+    rc = ensure_workspace(L.bytes);
     if (rc) return rc;
-    return dgemm_run(g_ws.base, o, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, d);
+    return dgemm_run(g_ws.base, L, o, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, d);
 }
 
 int emu_dgemm_noalloc(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda,
@@ -705,7 +665,8 @@ int emu_dgemm_noalloc(int64_t M, int64_t N, int64_t K, const double *A, int64_t 
     if (g_split_scope == EMU_SCOPE_KBIN)
         return fail(EMU_EINVAL, "emu_dgemm_noalloc: the K-binned scope needs the growing workspace");
     const DgemmOpts o = current_opts();
-    const size_t need = HDR + dgemm_layout(M, N, K, d, o).bytes;
+    const DgemmLayout L = dgemm_layout(d, M, N, K, o.scaled, device_cu_count());
+    const size_t need = HDR + L.bytes;
     if (need > NOALLOC_BYTES) {
         g_err = "emu_dgemm_noalloc: this problem needs " + std::to_string(need) +
                 " bytes of scratch, more than the fixed " + std::to_string(NOALLOC_BYTES);
@@ -713,7 +674,7 @@ int emu_dgemm_noalloc(int64_t M, int64_t N, int64_t K, const double *A, int64_t 
     }
     char *base = scratch_for_current_device(&rc);
     if (!base) return rc;
-    return dgemm_run(base, o, false, false, M, N, K, 1.0, A, lda, B, ldb, 0.0, C, ldc, d);
+    return dgemm_run(base, L, o, false, false, M, N, K, 1.0, A, lda, B, ldb, 0.0, C, ldc, d);
 }
 
 int emu_dgemm(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda, const double *B,

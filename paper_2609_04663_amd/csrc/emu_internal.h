@@ -25,42 +25,18 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dgemm_plan.h"
+
 namespace emu {
 
-constexpr int KBLK = 32;        // reduction indices per k-block (one LDS stage)
-constexpr int ROW_GROUP = 64;   // packed rows are padded to a multiple of this ...
-constexpr int KPANEL = 256;     // reduction panel B_K of the FP32/FP64 reconstruction
-
-// ... and of the GEMM tile that reads them (output tile rows for A, columns for B).
 constexpr int SGEMM_NT = 128;   // SGEMM output tiles: (192 or 128) x 128, or 64 x 64
-constexpr int DGEMM_NT = 64;
-// Slices of each operand that the products of depth d read (indices < 6).
-inline int dgemm_planes(int d) { return d < 6 ? d : 6; }
-constexpr int KB_PER_PANEL = KPANEL / KBLK;
 
 __host__ __device__ inline int swz(int64_t row) { return (int)((row >> 2) & 3); }
-
-// Memory-channel staggering of the packed operands.  With power-of-two sizes
-// the k-block stride (Rpad x 64 B) and the plane stride are multiples of a
-// large power of two, and every copy of a tile's k-block (all planes) lands in
-// the same few L2 channels.  Two skews break that: Rpad gets ROW_SKEW_TILES
-// extra tiles (never read by the GEMM), and consecutive planes are PLANE_SKEW elements further
-// apart than their KB x Rpad x 32 elements (a multiple of 512: planes stay
-// 1 KB aligned).
-constexpr int ROW_SKEW_TILES = 2;
-constexpr int64_t PLANE_SKEW = 2048;
-
-// Elements from one component plane to the next.
-__host__ __device__ inline int64_t plane_elems(int64_t KB, int64_t Rpad) {
-    return KB * Rpad * KBLK + PLANE_SKEW;
-}
 
 __host__ __device__ inline int64_t packed_index(int c, int64_t kb, int64_t row, int q, int64_t KB,
                                                 int64_t Rpad) {
     return c * plane_elems(KB, Rpad) + (kb * Rpad + row) * KBLK + 8 * (q ^ swz(row));
 }
-
-inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
 // Status bits (same values as EMU_STATUS_* in emu.h).
 constexpr unsigned ST_NAN = 1u, ST_RANGE = 2u, ST_SUBNORMAL = 4u, ST_OVERFLOW = 8u, ST_INEXACT = 16u,
@@ -255,17 +231,12 @@ hipError_t launch_gemm_f32_streamed(const float *A, int64_t lda, bool ta, const 
 hipError_t launch_gemm_f32(const uint16_t *Ap, const uint16_t *Bp, float *C, int64_t M, int64_t N,
                            int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc, float alpha,
                            float beta, int tile_m, int splits, float *part, hipStream_t s);
-// Packed layout of a depth-d DGEMM (M x N output, KB k-blocks of data) for the
-// kernel that will run it: A's rows are padded to a multiple of
-// dgemm_tile_rows (B's columns to DGEMM_NT), and the reduction to
-// dgemm_kb_padded k-blocks (some kernels run whole panels; the padding is zero).
-int64_t dgemm_tile_rows(int d, int64_t M, int64_t N, int64_t KB);
-int64_t dgemm_kb_padded(int d, int64_t M, int64_t N, int64_t KB);
 // sa, sb: row weights of A and column weights of B to restore (C_mn times
 // 2^(sa_m + sb_n)), or both null; skip_if: a word that, when nonzero, makes the
-// launch do nothing (the fallback is going to compute C), or null
+// launch do nothing (the fallback is going to compute C), or null; panels: the
+// operands are packed for the panel kernel (DgemmLayout)
 hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, int64_t M,
                            int64_t N, int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
                            const int *sa, const int *sb, double alpha, double beta, int d,
-                           const unsigned *skip_if, hipStream_t s);
+                           bool panels, const unsigned *skip_if, hipStream_t s);
 }  // namespace emu

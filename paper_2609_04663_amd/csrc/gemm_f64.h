@@ -39,12 +39,7 @@ struct DgemmArgs {
     const unsigned *skip_if;
 };
 
-// Persistent grid of the DGEMM kernels: one workgroup per CU (their LDS use
-// allows one), rounded down to a multiple of 8.
-inline int persistent_workgroups() {
-    const int cus = device_cu_count();
-    return cus < 8 ? 8 : cus / 8 * 8;
-}
+inline int persistent_workgroups() { return persistent_workgroups(device_cu_count()); }
 
 // gemm_f64s.hip: 32 x 32 x 16 MFMA, output tile (64 BM) x 64
 template <int D, int BM, int NS, bool ACC64_LDS>
@@ -55,7 +50,6 @@ hipError_t launch_s(const DgemmArgs &a, hipStream_t s);
 template <int D, int NS, bool ACC64_LDS, int BMW = 1, bool PERSIST_OK = true>
 hipError_t launch_w(const DgemmArgs &a, hipStream_t s);
 // gemm_f64t.hip: 32 x 32 x 16 MFMA over whole panels, output tile (64 t_bm(D)) x 64
-constexpr int t_bm(int d) { return d == 6 || d == 5 ? 1 : d == 4 || d == 3 ? 2 : 0; }
 template <int D>
 hipError_t launch_t64(const DgemmArgs &a, hipStream_t s);
 

@@ -26,40 +26,11 @@
 
 namespace emu {
 
-namespace {
-int64_t padded_panels(int64_t KB) { return (KB + KB_PER_PANEL - 1) / KB_PER_PANEL * KB_PER_PANEL; }
-
-// Whether a depth-d DGEMM of an M x N output with KB k-blocks runs on
-// gemm_f64t_kernel: d = 3 .. 6, at least a panel, and (64 BM) x 64 tiles that
-// fill the CUs (smaller grids keep the kernels with smaller tiles).  It pads
-// the reduction to whole panels: always worth it for K > 1024, and for shorter
-// reductions while the padding costs less than the kernel gains over the
-// others on whole panels (16384 x 16384 x 512: 3 / 8 / 30 / 15 % for d = 3 .. 6;
-// 3000 x 5000 x 300, padded to 512, was 12 / 22 % slower at d = 3 / 4, 13 % faster
-// at d = 5 and 15 % slower at d = 6).
-bool use_t64(int d, int64_t M, int64_t N, int64_t KB) {
-    if (d < 3 || d > 6 || KB < KB_PER_PANEL) return false;
-    constexpr int gain[7] = {0, 0, 0, 103, 107, 160, 112};   // per cent
-    if (KB <= 32 && padded_panels(KB) * 100 > KB * gain[d]) return false;
-    const int64_t mt = 64 * t_bm(d);
-    return ((M + mt - 1) / mt) * ((N + DGEMM_NT - 1) / DGEMM_NT) >= persistent_workgroups();
-}
-}  // namespace
-
-int64_t dgemm_tile_rows(int d, int64_t M, int64_t N, int64_t KB) {
-    if (use_t64(d, M, N, KB)) return 64 * t_bm(d);
-    return d == 1 ? 256 : d <= 3 ? 128 : 64;   // a multiple of every other kernel's tile
-}
-
-int64_t dgemm_kb_padded(int d, int64_t M, int64_t N, int64_t KB) {
-    return use_t64(d, M, N, KB) ? padded_panels(KB) : KB;
-}
-
 hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, int64_t M,
                            int64_t N, int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
                            const int *sa, const int *sb, double alpha, double beta, int d,
-                           const unsigned *skip_if, hipStream_t s) {
-    // First gemm_f64t_kernel where use_t64 says so.  The other calls of depths
+                           bool panels, const unsigned *skip_if, hipStream_t s) {
+    // First gemm_f64t_kernel where the plan packed the operands for it.  The other calls of depths
     // 1 .. 5 take the wide kernel's 64 x 64 tiles (BMW = 2) where it measured
     // faster than the 32 x 32 x 16 kernel: long reductions (K > 1024) of d = 2,
     // 4 and 5 (8, 2 and 5 % at 8192^3), and grids of d = 1 .. 3 whose 128- or
@@ -73,7 +44,7 @@ hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, in
         return ((M + mt - 1) / mt) * ((N + DGEMM_NT - 1) / DGEMM_NT) < pw;
     };
     const bool long_k = KB > 32;
-    if (use_t64(d, M, N, KB)) {
+    if (panels) {
         switch (d) {
             case 3: return launch_t64<3>(a, s);
             case 4: return launch_t64<4>(a, s);

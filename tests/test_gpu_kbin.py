@@ -107,6 +107,27 @@ def test_kbin_integers_exact(kbin):
     assert np.array_equal(got * 2.0 ** 8, np.rint(got * 2.0 ** 8))
 
 
+# (groups in ascending class order) 25 k-blocks in all, the last group 24 of them:
+# its panel-kernel layout would be larger than the area of the whole reduction
+@pytest.mark.parametrize("M,N,K,small", [(1600, 1600, 776, 8), (1344, 1536, 800, 32)])
+def test_kbin_group_of_another_layout(kbin, M, N, K, small):
+    A = S.make("normal", 1410, (M, K), np.float64)
+    B = S.make("normal", 1411, (K, N), np.float64)
+    big = np.random.default_rng(K).permutation(K)[:small]
+    B[big] *= 2.0 ** 16
+    classes = O.kbin_classes(A, B)
+    assert sorted(np.bincount(classes)[np.unique(classes)]) == [small, K - small]
+    rng = np.random.default_rng(M)
+    r = np.concatenate([[0, M - 1], rng.integers(0, M, 150)]).astype(np.int64)
+    c = np.concatenate([[0, N - 1], rng.integers(0, N, 150)]).astype(np.int64)
+    ref, st = O.emu_dgemm_entries(A, B, r, c, 10, scope=O.SCOPE_KBIN)
+    kbin.release_workspace()      # the call's own sizes, not those of a larger one before
+    kbin.domain_status()
+    got = kbin.dgemm(dev(A), dev(B), 10).cpu().numpy()
+    assert kbin.domain_status() == st == 0
+    assert bits_equal(np.ascontiguousarray(got[r, c]), ref)
+
+
 def test_kbin_single_class_is_rowcol(kbin):
     A = S.make("uniform", 1407, (150, 800), np.float64)
     B = S.make("uniform", 1408, (800, 70), np.float64)
