@@ -145,8 +145,9 @@ int emu_dgemm(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda, con
    holds on every GPU it runs on until the process ends (its address is looked
    up on the first call on each device, which also clears its status word with
    a kernel).  A call whose packed planes (2 min(d, 6) bytes per element of
-   both operands, rows padded to whole tiles and K to whole k-blocks) plus a
-   2 KB header and, in the ROWCOL scope, 12 bytes per row of A and column of B
+   both operands; rows padded to whole tiles and two tiles more, K to whole
+   k-blocks of 32, or for K > 1024 at d = 3 .. 6 with at least as many output
+   tiles as CUs to whole panels of 256) plus a 2 KB header and, in the ROWCOL scope, 12 bytes per row of A and column of B
    exceed 64 MiB returns EMU_ENOMEM before launching anything (square
    problems up to about M = N = K = 1500 at nprod = 21, 2100 at nprod = 6).  All calls on one GPU
    share that array: calls that overlap in time on one GPU (two streams, two

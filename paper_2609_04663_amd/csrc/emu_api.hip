@@ -56,6 +56,8 @@ std::string g_err;
 struct Workspace {
     char *base = nullptr;
     size_t bytes = 0;
+    size_t refused = (size_t)-1;   // smallest size that the device could not give
+    unsigned status = 0;           // the status word while nothing is held after a refusal
 } g_ws;
 
 constexpr size_t HDR = 2048;
@@ -81,7 +83,7 @@ int ensure_workspace(size_t need) {
     need += HDR;
     if (need <= g_ws.bytes) return EMU_OK;
     if (need > workspace_limit()) return fail(EMU_ENOMEM, "workspace would exceed EMU_WORKSPACE_LIMIT");
-    unsigned status = 0;
+    unsigned status = g_ws.status;
     if (g_ws.base) {
         hipError_t e = hipStreamSynchronize(g_stream);
         if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
@@ -96,6 +98,8 @@ int ensure_workspace(size_t need) {
     hipError_t e = hipMalloc(&p, need);
     if (e != hipSuccess || !p) {
         (void)hipGetLastError();
+        if (need < g_ws.refused) g_ws.refused = need;
+        g_ws.status = status;
         return fail(EMU_ENOMEM, "hipMalloc of the workspace failed");
     }
     e = hipMemcpy(p, &status, sizeof(status), hipMemcpyHostToDevice);
@@ -110,7 +114,29 @@ int ensure_workspace(size_t need) {
     }
     g_ws.base = (char *)p;
     g_ws.bytes = need;
+    g_ws.status = 0;
     return EMU_OK;
+}
+
+// Grows the workspace for the layout of a depth-d DGEMM and `rest` more bytes.
+// The panel kernel packs short reductions into up to 1.6 times the bytes of the
+// other kernels: where those are not to be had (EMU_WORKSPACE_LIMIT, or the
+// device has no memory left), the layout is that of the other kernels.  A size
+// that the device refused is not tried again for it on every call.
+int ensure_layout(int d, int64_t M, int64_t N, int64_t K, bool scaled, size_t rest, DgemmLayout *L) {
+    const size_t cap = workspace_limit();
+    size_t most = cap < g_ws.refused ? cap : g_ws.refused - 1;
+    if (most < g_ws.bytes) most = g_ws.bytes;   // held already
+    const int cus = device_cu_count();
+    *L = dgemm_layout(d, M, N, K, scaled, cus, most > HDR + rest ? most - HDR - rest : 0);
+    int rc = ensure_workspace(L->bytes + rest);
+    if (rc == EMU_ENOMEM && L->panels) {
+        *L = dgemm_layout(d, M, N, K, scaled, cus, 0);
+        if (L->panels) return rc;   // a long reduction has no other layout
+        rc = ensure_workspace(L->bytes + rest);
+        if (rc == EMU_OK) g_err.clear();
+    }
+    return rc;
 }
 
 // Phase profiling: a fixed pool of event triples, created by emu_profile_enable.
@@ -289,6 +315,8 @@ const char *emu_last_error(void) { return g_err.c_str(); }
 int64_t emu_workspace_bytes(void) { return (int64_t)g_ws.bytes; }
 
 int emu_release_workspace(void) {
+    g_ws.refused = (size_t)-1;
+    g_ws.status = 0;
     if (!g_ws.base) return EMU_OK;
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
@@ -530,8 +558,7 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
     const bool direct = alpha == 1.0 && beta == 0.0;
     auto up = [](size_t x) { return (x + 255) / 256 * 256; };
     // workspace after the area that the groups' DGEMMs share (planes and weights)
-    const size_t area = dgemm_layout(d, M, N, K, true, device_cu_count()).bytes;
-    size_t off = up(area);
+    size_t off = 0;
     const int64_t MN = M > N ? M : N;
     const size_t o_sa = off;  off = up(off + (size_t)M * 4);
     const size_t o_sb = off;  off = up(off + (size_t)N * 4);
@@ -543,9 +570,11 @@ int dgemm_kbin(bool ta, bool tb, int64_t M, int64_t N, int64_t K, double alpha, 
     const size_t o_ga = off;  off = up(off + (size_t)M * K * 8);
     const size_t o_gb = off;  off = up(off + (size_t)K * N * 8);
     const size_t o_p = off;   off = up(off + (direct ? 0 : (size_t)M * N * 8));
-    int rc = ensure_workspace(off);
+    DgemmLayout whole;
+    int rc = ensure_layout(d, M, N, K, true, off, &whole);
     if (rc) return rc;
-    char *base = g_ws.base, *w = g_ws.base + HDR;
+    const size_t area = whole.bytes;
+    char *base = g_ws.base, *w = g_ws.base + HDR + area;
     int *sa = reinterpret_cast<int *>(w + o_sa), *sb = reinterpret_cast<int *>(w + o_sb);
     auto *mx = reinterpret_cast<unsigned long long *>(w + o_mx);
     auto *ma = reinterpret_cast<unsigned long long *>(w + o_ma);
@@ -649,8 +678,8 @@ int emu_dgemm_ex(char transa, char transb, int64_t M, int64_t N, int64_t K, doub
     if (g_split_scope == EMU_SCOPE_KBIN)
         return dgemm_kbin(ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, d);
     const DgemmOpts o = current_opts();
-    const DgemmLayout L = dgemm_layout(d, M, N, K, o.scaled, device_cu_count());
-    rc = ensure_workspace(L.bytes);
+    DgemmLayout L;
+    rc = ensure_layout(d, M, N, K, o.scaled, 0, &L);
     if (rc) return rc;
     return dgemm_run(g_ws.base, L, o, ta, tb, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, d);
 }
@@ -665,7 +694,8 @@ int emu_dgemm_noalloc(int64_t M, int64_t N, int64_t K, const double *A, int64_t 
     if (g_split_scope == EMU_SCOPE_KBIN)
         return fail(EMU_EINVAL, "emu_dgemm_noalloc: the K-binned scope needs the growing workspace");
     const DgemmOpts o = current_opts();
-    const DgemmLayout L = dgemm_layout(d, M, N, K, o.scaled, device_cu_count());
+    const DgemmLayout L =
+        dgemm_layout(d, M, N, K, o.scaled, device_cu_count(), NOALLOC_BYTES - HDR);
     const size_t need = HDR + L.bytes;
     if (need > NOALLOC_BYTES) {
         g_err = "emu_dgemm_noalloc: this problem needs " + std::to_string(need) +

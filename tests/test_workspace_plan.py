@@ -1,6 +1,7 @@
 """Workspace sizes of the emulated DGEMM, evaluated by a host program that
 includes the library's own plan (no GPU): every group of a K-binned call fits
-the area that the call reserves for its groups."""
+the area that the call reserves for its groups, and a short reduction fits a
+limit whenever the smaller of its two layouts does."""
 import os
 import subprocess
 
@@ -75,3 +76,23 @@ def test_group_of_24_of_25_k_blocks(plan):
     assert panels and group > whole
     fits, panels = plan("layout", 4, 1600, 1600, 768, 1, whole)
     assert not panels and fits <= whole
+
+
+# the fixed scratch of emu_dgemm_noalloc: 64 MiB less its header
+SCRATCH = (64 << 20) - 2048
+
+
+@pytest.mark.parametrize("d,n,k", [(5, 6408, 320), (5, 10304, 289), (5, 4232, 545), (5, 5632, 545),
+                                   (5, 3144, 800), (5, 4032, 800), (4, 7944, 512), (4, 3904, 1000)])
+def test_short_reductions_within_the_scratch(plan, d, n, k):
+    want, panels = plan("layout", d, n, n, k, 0, NO_LIMIT)
+    got, other = plan("layout", d, n, n, k, 0, SCRATCH)
+    assert want > SCRATCH and panels and got <= SCRATCH and not other
+    # 2 d bytes an entry, rows to 64 and two tiles more, whole k-blocks of 32
+    rows, kb = -(-n // 64) * 64 + 128, -(-k // 32)
+    assert got == -(-2 * d * 2 * (kb * rows * 32 + 2048) // 256) * 256
+
+
+def test_long_reductions_have_one_layout(plan):
+    size, panels = plan("layout", 5, 4000, 4000, 1025, 0, NO_LIMIT)
+    assert panels and plan("layout", 5, 4000, 4000, 1025, 0, size - 1) == [size, 1]

@@ -79,6 +79,56 @@ def test_noalloc_refuses_sizes_beyond_the_scratch(emu):
     assert L.emu_dgemm_noalloc(4, 4, 4, P, 4, P, 4, P, 4, 7) == emu.EMU_EINVAL
 
 
+# fit the scratch in the packing of the other kernels, not in the panel kernel's
+# whole panels (10, 25 and 32 k-blocks) or taller tiles
+@pytest.mark.parametrize("M,N,K,nprod", [(6408, 6408, 320, 15), (3144, 3144, 800, 15),
+                                         (3848, 3848, 1000, 10)])
+def test_noalloc_short_reductions_near_the_scratch(emu, M, N, K, nprod):
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randn((M, K), generator=g, device="cuda", dtype=torch.float64)
+    B = torch.randn((K, N), generator=g, device="cuda", dtype=torch.float64)
+    C = torch.full((M, N), float("nan"), dtype=torch.float64, device="cuda")
+    assert noalloc(emu, A, B, C, nprod) == emu.EMU_OK, emu.lib().emu_last_error()
+    ref = emu.dgemm(A, B, nprod)              # the panel kernel, on the workspace
+    assert torch.equal(C.view(torch.int64), ref.view(torch.int64))
+    emu.release_workspace()
+
+
+@pytest.mark.parametrize("scope", ["SCOPE_OPERAND", "SCOPE_KBIN"])
+def test_workspace_limit_leaves_the_panel_kernel(emu, monkeypatch, scope):
+    """A short reduction whose panel packing exceeds EMU_WORKSPACE_LIMIT runs on
+    the other kernels, with the same bits; a longer one is refused."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A = torch.randn((1600, 300), generator=g, device="cuda", dtype=torch.float64)
+    B = torch.randn((300, 1600), generator=g, device="cuda", dtype=torch.float64)
+    L = torch.randn((1600, 1100), generator=g, device="cuda", dtype=torch.float64)
+    emu.set_split_scope(getattr(emu, scope))
+    try:
+        emu.release_workspace()
+        ref = emu.dgemm(A, B, 15)
+        panels = emu.workspace_bytes()
+        emu.release_workspace()
+        monkeypatch.setenv("EMU_WORKSPACE_LIMIT", str(panels - 1))
+        got = emu.dgemm(A, B, 15)
+        plain = emu.workspace_bytes()
+        assert 0 < plain < panels
+        assert torch.equal(got.view(torch.int64), ref.view(torch.int64))
+        emu.release_workspace()
+        monkeypatch.setenv("EMU_WORKSPACE_LIMIT", str(plain - 1))
+        with pytest.raises(emu.EmuError):
+            emu.dgemm(A, B, 15)
+        monkeypatch.delenv("EMU_WORKSPACE_LIMIT")
+        emu.dgemm(L, L.T.contiguous(), 15)
+        long = emu.workspace_bytes()
+        emu.release_workspace()
+        monkeypatch.setenv("EMU_WORKSPACE_LIMIT", str(long - 1))
+        with pytest.raises(emu.EmuError):
+            emu.dgemm(L, L.T.contiguous(), 15)
+    finally:
+        emu.set_split_scope(emu.SCOPE_OPERAND)
+        emu.release_workspace()
+
+
 def test_noalloc_reports_status(emu):
     A = dev(np.ldexp(S.make("uniform", 921, (60, 300), np.float64), -45))
     B = dev(np.ldexp(S.make("uniform", 922, (300, 40), np.float64), -45))
