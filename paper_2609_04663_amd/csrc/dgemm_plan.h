@@ -67,17 +67,34 @@ constexpr int64_t SHORT_KB = 32;
 // Whether a depth-d DGEMM of an M x N output with KB k-blocks of data is to run
 // on the panel kernel: d = 3 .. 6, at least a panel, and (64 BM) x 64 tiles that
 // fill the CUs (smaller grids keep the kernels with smaller tiles).  It pads
-// the reduction to whole panels: always worth it for K > 1024, and for shorter
-// reductions while the padding costs less than the kernel gains over the
-// others on whole panels (16384 x 16384 x 512: 3 / 8 / 30 / 15 % for d = 3 .. 6;
-// 3000 x 5000 x 300, padded to 512, was 12 / 22 % slower at d = 3 / 4, 13 % faster
-// at d = 5 and 15 % slower at d = 6).
+// the reduction to whole panels: always worth it for K > 1024.  Shorter
+// reductions take it where two rules hold:
+//   * the padding costs less than the kernel gains over the others on whole
+//     panels (16384 x 16384 x 512: 3 / 8 / 30 / 15 % for d = 3 .. 6; 3000 x 5000
+//     x 300, padded to 512, was 12 / 22 % slower at d = 3 / 4, 13 % faster at
+//     d = 5 and 15 % slower at d = 6);
+//   * its rounds of workgroups cost no more than those of the kernel it replaces.
+//     For d = 3 and 5 that one has the same tiles, for d = 4 and 6 tiles of half
+//     the height, so that a panel round counts as two of them, over the gain
+//     per round (d = 4 17 %, d = 6 25 %).  Product GEMM at K = 1024, other kernel / panel
+//     kernel, us (rounds): d = 4, 1344 x 1536 44.8 (2) / 67.1 (2), 1600 x 1600 61.3 (3)
+//     / 67.0 (2), 2176 x 1536 80.9 (4) / 68.0 (2), 3000 x 3000 178.9 (9) / 168.3 (5);
+//     d = 6, 1088 x 1024 66.1 (3) / 68.7 (2), 1280 x 1280 86.4 (4) / 69.2 (2),
+//     1472 x 1472 106.4 (5) / 103.9 (3).
 inline bool panel_kernel_wanted(int d, int64_t M, int64_t N, int64_t KB, int cus) {
     if (d < 3 || d > 6 || KB < KB_PER_PANEL) return false;
-    constexpr int gain[7] = {0, 0, 0, 103, 107, 160, 112};   // per cent
-    if (KB <= SHORT_KB && round_up(KB, KB_PER_PANEL) * 100 > KB * gain[d]) return false;
-    const int64_t mt = 64 * t_bm(d);
-    return ((M + mt - 1) / mt) * ((N + DGEMM_NT - 1) / DGEMM_NT) >= persistent_workgroups(cus);
+    const int64_t mt = 64 * t_bm(d), nt_n = (N + DGEMM_NT - 1) / DGEMM_NT;
+    const int64_t pw = persistent_workgroups(cus), tiles = (M + mt - 1) / mt * nt_n;
+    if (tiles < pw) return false;
+    if (KB > SHORT_KB) return true;
+    constexpr int gain[7] = {0, 0, 0, 103, 107, 160, 112};         // per cent
+    constexpr int round_gain[7] = {0, 0, 0, 0, 117, 0, 125};
+    const int64_t padded = round_up(KB, KB_PER_PANEL);
+    if (padded * 100 > KB * gain[d]) return false;
+    if (d == 3 || d == 5) return true;
+    const int64_t rounds = (tiles + pw - 1) / pw;
+    const int64_t half_tiles = (M + mt / 2 - 1) / (mt / 2) * nt_n;
+    return rounds * 2 * padded * 100 <= (half_tiles + pw - 1) / pw * KB * round_gain[d];
 }
 
 // Scale-aware split scratch: 64-bit maxima for the nA rows of A and the nB

@@ -109,7 +109,8 @@ def test_kbin_integers_exact(kbin):
 
 # (groups in ascending class order) 25 k-blocks in all, the last group 24 of them:
 # its panel-kernel layout would be larger than the area of the whole reduction
-@pytest.mark.parametrize("M,N,K,small", [(1600, 1600, 776, 8), (1344, 1536, 800, 32)])
+@pytest.mark.parametrize("M,N,K,small", [(1600, 1600, 776, 8), (1344, 1536, 800, 32),
+                                           (2112, 1536, 776, 8)])
 def test_kbin_group_of_another_layout(kbin, M, N, K, small):
     A = S.make("normal", 1410, (M, K), np.float64)
     B = S.make("normal", 1411, (K, N), np.float64)

@@ -70,11 +70,11 @@ def test_kbin_groups_fit_the_shared_area(plan):
 
 
 def test_group_of_24_of_25_k_blocks(plan):
-    whole, panels = plan("layout", 4, 1600, 1600, 776, 1, NO_LIMIT)
+    whole, panels = plan("layout", 4, 2112, 1536, 776, 1, NO_LIMIT)
     assert not panels
-    group, panels = plan("layout", 4, 1600, 1600, 768, 1, NO_LIMIT)
+    group, panels = plan("layout", 4, 2112, 1536, 768, 1, NO_LIMIT)
     assert panels and group > whole
-    fits, panels = plan("layout", 4, 1600, 1600, 768, 1, whole)
+    fits, panels = plan("layout", 4, 2112, 1536, 768, 1, whole)
     assert not panels and fits <= whole
 
 
@@ -96,3 +96,15 @@ def test_short_reductions_within_the_scratch(plan, d, n, k):
 def test_long_reductions_have_one_layout(plan):
     size, panels = plan("layout", 5, 4000, 4000, 1025, 0, NO_LIMIT)
     assert panels and plan("layout", 5, 4000, 4000, 1025, 0, size - 1) == [size, 1]
+
+
+# 128 x 64 tiles at d = 4 and 64 x 64 ones at d = 6 against tiles of half the
+# height: 2 rounds of 256 for 2, for 3, for 4; 3 for 5; 5 for 9
+@pytest.mark.parametrize("d,m,n,panels", [
+    (4, 1344, 1536, 0), (4, 1600, 1600, 0), (4, 2176, 1536, 1), (4, 3000, 3000, 1),
+    (6, 1088, 1024, 0), (6, 1280, 1280, 1), (6, 1472, 1472, 1), (4, 1024, 1024, 0),
+    (3, 1344, 1536, 1), (5, 1088, 1024, 1)])
+def test_short_reductions_by_rounds(plan, d, m, n, panels):
+    assert plan("layout", d, m, n, 1024, 0, NO_LIMIT)[1] == panels
+    # longer ones as long as the tiles fill the CUs
+    assert plan("layout", d, m, n, 1025, 0, NO_LIMIT)[1] == (m * n > 1024 * 1024 or d != 4)
