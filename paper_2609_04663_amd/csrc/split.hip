@@ -160,6 +160,9 @@ struct F64SplitArgs {
     int units0;           // replay work units of operand 0; the rest serve operand 1
 };
 
+// Eq. (bf16rangefp64): nonzero magnitudes from 2^-126 to (2 - 2^-7) 2^127.
+constexpr double DOMAIN_LO = 0x1p-126, DOMAIN_HI = 0x1.fep127;
+
 // The block's operand (selected, not indexed, so that the arguments stay in the
 // kernel-argument segment), its block index and block count within it.
 __device__ inline const F64SplitOperand &operand_of_block(const F64SplitArgs &a, int &b, int &nb) {
@@ -194,7 +197,6 @@ __global__ __launch_bounds__(MAX_THREADS) void f64_maxabs_kernel(F64SplitArgs a)
     }
     double m = 0.0;
     bool nonfinite = false, range = false;
-    const double lo = 0x1p-126, hi = 0x1.fep127;   // (2 - 2^-7) 2^127
     const bool one_row = op.ldx == op.cols;
     const int64_t rows = one_row ? 1 : op.rows;
     const int64_t cols = one_row ? op.rows * op.cols : op.cols;
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(MAX_THREADS) void f64_maxabs_kernel(F64SplitArgs a)
             const double ax = fabs(x[u]);
             const bool fin = __builtin_isfinite(x[u]);
             nonfinite |= !fin;
-            range |= fin && x[u] != 0.0 && (ax < lo || ax > hi);
+            range |= fin && x[u] != 0.0 && (ax < DOMAIN_LO || ax > DOMAIN_HI);
             m = fmax(m, fin ? ax : 0.0);
         }
     }
@@ -238,10 +240,11 @@ __global__ __launch_bounds__(MAX_THREADS) void f64_maxabs_kernel(F64SplitArgs a)
 }
 
 // The eight entries of work item (pair, thread): packed row ic.prow, reduction
-// indices k0 .. k0 + 7; zeros outside the operand; weights applied.
+// indices k0 .. k0 + 7; zeros outside the operand; weights applied.  scan: look
+// for scaled entries below the domain (ST_RANGE into st), see f64_weights_kernel.
 template <bool AS_B>
 __device__ __forceinline__ void load8_f64(const F64SplitOperand &op, const ItemCoords &ic,
-                                          double (&x)[8]) {
+                                          bool scan, double (&x)[8], unsigned &st) {
     const int64_t prow_lim = AS_B ? op.cols : op.rows;
     const int64_t k_lim = AS_B ? op.rows : op.cols;
     const int64_t k0 = ic.kb * KBLK + ic.q * 8, ldx = op.ldx;
@@ -270,6 +273,11 @@ __device__ __forceinline__ void load8_f64(const F64SplitOperand &op, const ItemC
         const int wexp = ic.prow < prow_lim ? -op.sc[ic.prow] : 0;   // weight 2^-s
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = ldexp(x[i], wexp);
+        if (scan) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (x[i] != 0.0 && fabs(x[i]) < DOMAIN_LO) st |= ST_RANGE;
+        }
     }
 }
 
@@ -292,7 +300,7 @@ __device__ inline bool plain_level(int v) { return v != V_ZERO && v >= -118 && v
 template <bool AS_B, bool WRITE_THROUGH>
 __device__ __forceinline__ void split_f64_pass(const F64SplitOperand &op, int64_t KB, int b, int nb,
                                                const int (&v)[6], int r0, int nlev, double cst,
-                                               double (&mx)[6], unsigned &st) {
+                                               bool scan, double (&mx)[6], unsigned &st) {
     double sig[6];
     bool plain[6];
 #pragma unroll
@@ -305,7 +313,7 @@ __device__ __forceinline__ void split_f64_pass(const F64SplitOperand &op, int64_
     for (int64_t pair = b; pair < npairs; pair += nb) {
         const ItemCoords ic = item_coords(pair, RG);
         double x[8];
-        load8_f64<AS_B>(op, ic, x);
+        load8_f64<AS_B>(op, ic, scan, x, st);
         // level by level over the eight entries: the branches on the (uniform)
         // form of a level are taken once per item, not once per entry
 #pragma unroll
@@ -359,8 +367,8 @@ __device__ __forceinline__ void split_f64_pass(const F64SplitOperand &op, int64_
 // per entry and level, five of them FP64.
 template <int NLEV, bool AS_B>
 __device__ __forceinline__ void split_f64_plain(const F64SplitOperand &op, int64_t KB, int b, int nb,
-                                                const int (&v)[6], double cst, double (&mx)[6],
-                                                unsigned &st) {
+                                                const int (&v)[6], double cst, bool scan,
+                                                double (&mx)[6], unsigned &st) {
     double sig[NLEV];
 #pragma unroll
     for (int r = 0; r < NLEV; ++r) sig[r] = ldexp(cst, v[r] + 45);
@@ -375,7 +383,7 @@ __device__ __forceinline__ void split_f64_plain(const F64SplitOperand &op, int64
         ic.prow = (int64_t)(pair - kb * RG) * ROWS_PER_BLOCK + (threadIdx.x >> 2);
         ic.q = threadIdx.x & 3;
         double x[8];
-        load8_f64<AS_B>(op, ic, x);
+        load8_f64<AS_B>(op, ic, scan, x, st);
         unsigned outp[NLEV][4];
 #pragma unroll
         for (int i = 0; i < 8; i += 2) {
@@ -430,16 +438,23 @@ __global__ __launch_bounds__(SPLIT_THREADS) void split_f64_kernel(F64SplitArgs a
     int b, nb;
     const F64SplitOperand &op = operand_of_block(a, b, nb);
     const int nmax = a.nops > 1 && (int)blockIdx.x >= a.blocks0 ? a.max1 : a.max0;
-    // the operand-wide maximum from the partials of f64_maxabs_kernel
+    // the operand-wide maximum from the partials of f64_maxabs_kernel, or of
+    // f64_weights_kernel, whose sign says that the entries are to be looked through
     const double *part = partial_max(op, a.KB, 0);
     double m0 = 0.0;
     static_assert(MAX_BLOCKS <= SPLIT_THREADS, "one partial per thread");
     if ((int)threadIdx.x < nmax) m0 = part[threadIdx.x];
-    m0 = wave_max(m0);
-    if ((threadIdx.x & 63) == 0) red[0][threadIdx.x >> 6] = m0;
+    const bool wave_scan = op.sc != nullptr && __any(signbit(m0));
+    m0 = wave_max(fabs(m0));
+    if ((threadIdx.x & 63) == 0) red[0][threadIdx.x >> 6] = wave_scan ? -m0 : m0;
     __syncthreads();
+    bool scan = false;
 #pragma unroll
-    for (int i = 0; i < SPLIT_THREADS / 64; ++i) m0 = fmax(m0, red[0][i]);
+    for (int i = 0; i < SPLIT_THREADS / 64; ++i) {
+        m0 = fmax(m0, fabs(red[0][i]));
+        scan |= signbit(red[0][i]);
+    }
+    scan = __builtin_amdgcn_readfirstlane(scan);
     m0 = __longlong_as_double(((long long)__builtin_amdgcn_readfirstlane((int)(dbits(m0) >> 32)) << 32) |
                               (unsigned)__builtin_amdgcn_readfirstlane((int)dbits(m0)));
     int v[6];
@@ -450,11 +465,11 @@ __global__ __launch_bounds__(SPLIT_THREADS) void split_f64_kernel(F64SplitArgs a
     double mx[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     unsigned st = 0;
     if (plain_level(v[0]) && plain_level(v[NLEV - 1])) {   // v descends
-        if (op.as_b) split_f64_plain<NLEV, true>(op, a.KB, b, nb, v, cst, mx, st);
-        else split_f64_plain<NLEV, false>(op, a.KB, b, nb, v, cst, mx, st);
+        if (op.as_b) split_f64_plain<NLEV, true>(op, a.KB, b, nb, v, cst, scan, mx, st);
+        else split_f64_plain<NLEV, false>(op, a.KB, b, nb, v, cst, scan, mx, st);
     } else {
-        if (op.as_b) split_f64_pass<true, false>(op, a.KB, b, nb, v, 0, NLEV, cst, mx, st);
-        else split_f64_pass<false, false>(op, a.KB, b, nb, v, 0, NLEV, cst, mx, st);
+        if (op.as_b) split_f64_pass<true, false>(op, a.KB, b, nb, v, 0, NLEV, cst, scan, mx, st);
+        else split_f64_pass<false, false>(op, a.KB, b, nb, v, 0, NLEV, cst, scan, mx, st);
     }
     st = block_or(st);
     if ((threadIdx.x & 63) == 0 && st) atomicOr(a.status, st);
@@ -677,8 +692,8 @@ __global__ __launch_bounds__(SPLIT_THREADS, 4) void f64_replay_kernel(F64SplitAr
         if (r0 >= 0) {
             double mx[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             unsigned st = 0;
-            if (op.as_b) split_f64_pass<true, true>(op, a.KB, b, nb, v, r0, nlev, cst, mx, st);
-            else split_f64_pass<false, true>(op, a.KB, b, nb, v, r0, nlev, cst, mx, st);
+            if (op.as_b) split_f64_pass<true, true>(op, a.KB, b, nb, v, r0, nlev, cst, false, mx, st);
+            else split_f64_pass<false, true>(op, a.KB, b, nb, v, r0, nlev, cst, false, mx, st);
             st = block_or(st);
             if ((threadIdx.x & 63) == 0 && st) atomicOr(a.status, st);
             block_level_max(mx, r0, nlev, red);
@@ -911,8 +926,11 @@ __global__ void stats_init_kernel(unsigned long long *mx, unsigned long long *mn
 // From the statistics of an operand's packed rows: their weights, and in place of
 // f64_maxabs_kernel the level-0 maximum of the scaled operand, its range check
 // and the cleared state.  A scaled magnitude is at most 1, so only entries below
-// 2^-126 leave the range.  Where the smallest one underflows to an exact zero
-// (which is in the domain), the row's entries are looked through for others.
+// 2^-126 leave the range.  Where the smallest one of a row underflows to an exact
+// zero (which is in the domain), others of the row may leave it: the sign of the
+// block's maximum then tells the split pass to look at every entry.  (A walk of the
+// row by the thread here took 2.2 ms for one such row of 16384 entries, in a call of
+// 0.25.)
 __global__ __launch_bounds__(SPLIT_THREADS) void f64_weights_kernel(F64SplitArgs a) {
     __shared__ double red[SPLIT_THREADS / 64];
     int b, nb;
@@ -921,10 +939,9 @@ __global__ __launch_bounds__(SPLIT_THREADS) void f64_weights_kernel(F64SplitArgs
         unsigned *w = reinterpret_cast<unsigned *>(op.st);
         for (int i = threadIdx.x; i < (int)(sizeof(F64SplitState) / 4); i += SPLIT_THREADS) w[i] = 0u;
     }
-    const int64_t n = op.as_b ? op.cols : op.rows, len = op.as_b ? op.rows : op.cols;
-    const double lo = 0x1p-126;
+    const int64_t n = op.as_b ? op.cols : op.rows;
     double m = 0.0;
-    bool range = false;
+    bool range = false, scan = false;
     for (int64_t p = (int64_t)b * SPLIT_THREADS + threadIdx.x; p < n; p += (int64_t)nb * SPLIT_THREADS) {
         const double mx = __longlong_as_double((long long)op.mx[p]);
         const int s = mx > 0.0 ? ceil_log2_pos(mx) : 0;
@@ -932,27 +949,24 @@ __global__ __launch_bounds__(SPLIT_THREADS) void f64_weights_kernel(F64SplitArgs
         m = fmax(m, ldexp(mx, -s));
         if (mx > 0.0) {
             const double t = ldexp(__longlong_as_double((long long)op.mn[p]), -s);
-            if (t > 0.0) {
-                range |= t < lo;
-            } else {
-                for (int64_t i = 0; i < len && !range; ++i) {
-                    const double x = op.X[op.as_b ? i * op.ldx + p : p * op.ldx + i];
-                    const double y = fabs(ldexp(x, -s));
-                    range = y > 0.0 && y < lo;
-                }
-            }
+            range |= t > 0.0 && t < DOMAIN_LO;
+            scan |= t == 0.0;
         }
     }
     m = wave_max(m);
+    scan = __any(scan);
     const unsigned flags = block_or(range ? ST_RANGE : 0u);
     if ((threadIdx.x & 63) == 0) {
-        red[threadIdx.x >> 6] = m;
+        red[threadIdx.x >> 6] = scan ? -m : m;
         if (flags) atomicOr(a.status, flags);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < SPLIT_THREADS / 64; ++i) m = fmax(m, red[i]);
-        partial_max(op, a.KB, 0)[b] = m;
+        for (int i = 1; i < SPLIT_THREADS / 64; ++i) {
+            m = fmax(m, fabs(red[i]));
+            scan |= signbit(red[i]);
+        }
+        partial_max(op, a.KB, 0)[b] = scan ? -m : m;
     }
 }
 

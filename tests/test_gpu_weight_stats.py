@@ -101,3 +101,57 @@ def test_rowcol_extents(emu, M, N, K):
     finally:
         emu.set_split_scope(emu.SCOPE_OPERAND)
     assert np.array_equal(bits(C[r, c]), bits(ref))
+
+
+@pytest.mark.parametrize("as_b", [0, 1])
+@pytest.mark.parametrize("low", [2.0 ** -60, 2.0 ** 800, None])
+def test_underflowing_rows_far_apart(emu, low, as_b):
+    """A row that underflows in one block's share, the entry below the domain in
+    another's: the whole operand is looked through, in one pass."""
+    X = S.make("uniform", 10, (600, 2100), np.float64)
+    X[[7, 597]] = 0.0
+    X[7, [0, 9]] = [2.0 ** 1000, 2.0 ** -100]
+    X[597, [3, 64, 2099]] = [2.0 ** 1000, 2.0 ** -100, low or 2.0 ** 990]
+    ref, v, _, st = O.split_f64(np.ldexp(X, -O.scale_exponents(X)[:, None]))
+    assert bool(st & O.ST_RANGE) == (low is not None)
+    emu.set_split_scope(emu.SCOPE_ROWCOL)
+    try:
+        emu.domain_status()
+        got, vg = emu.split_f64(dev(X.T if as_b else X), as_b=bool(as_b))
+        assert emu.domain_status() == st
+    finally:
+        emu.set_split_scope(emu.SCOPE_OPERAND)
+    g = got.cpu().numpy().view(np.uint16)
+    assert np.array_equal(vg.cpu().numpy(), v)
+    assert np.array_equal(g.transpose(0, 2, 1) if as_b else g, ref)
+
+
+@pytest.mark.parametrize("which", ["A", "B"])
+def test_underflowing_row_costs_no_walk(emu, which):
+    """One subnormal entry among ordinary ones: the call takes about as long as
+    without it (twice is far above what the timer varies by; one thread walking
+    the row of 16384 entries took ten times as long)."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randn((256, 16384), generator=g, device="cuda", dtype=torch.float64)
+    B = torch.randn((16384, 256), generator=g, device="cuda", dtype=torch.float64)
+
+    def ms():
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        t = []
+        for _ in range(9):
+            ev[0].record()
+            emu.dgemm(A, B, 6)
+            ev[1].record()
+            ev[1].synchronize()
+            t.append(ev[0].elapsed_time(ev[1]))
+        return sorted(t)[4]
+    emu.set_split_scope(emu.SCOPE_ROWCOL)
+    try:
+        plain = ms()
+        X = A if which == "A" else B
+        X[37, 101] = 5e-324
+        X[37 if which == "A" else 3, 102 if which == "A" else 101] = 5.0
+        walked = ms()
+    finally:
+        emu.set_split_scope(emu.SCOPE_OPERAND)
+    assert walked < 2.0 * plain, (plain, walked)
