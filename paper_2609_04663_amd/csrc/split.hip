@@ -351,9 +351,9 @@ __device__ __forceinline__ void split_f64_pass(const F64SplitOperand &op, int64_
             }
             u16 *dst = op.P + packed_index(r, ic.kb, ic.prow, ic.q, KB, op.Rpad);
             if constexpr (WRITE_THROUGH) {
-                // a 16-byte store of device scope (the wait state lets the
+                // a 16-byte store of device scope (the two wait states let the
                 // store read its data before a VALU instruction may write it)
-                asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0"
+                asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1"
                              :: "v"(dst), "v"(outp) : "memory");
             } else {
                 *reinterpret_cast<u16x8 *>(dst) = outp;
