@@ -57,8 +57,7 @@ struct F64ReplaySlot {
     int pad;
 };
 struct alignas(64) F64SplitState {
-    unsigned seen;                   // bit r: some block's maximum of level r has the
-                                     // speculated exponent
+    unsigned seen;                   // the split pass's marks of the levels
     int v[6];                        // speculated chain
     int vfinal[6];
     // replay work distribution (operand 0's are used), each on cache lines of its own

@@ -114,10 +114,12 @@ __global__ __launch_bounds__(SPLIT_THREADS) void split_f32_kernel(F32SplitArgs a
 //   f64_maxabs_kernel   the level-0 maximum, one partial per block;
 //   split_f64_kernel    every block reduces those partials, speculates the
 //                       chain, writes all slices, leaves its maxima of the
-//                       levels and marks the levels whose exponent it confirms;
-//   f64_replay_kernel   returns at once when every level is confirmed (the
-//                       largest residual of a level has the speculated
-//                       exponent; it can never have a larger one).  Otherwise
+//                       levels and marks the levels whose exponent it confirms,
+//                       finds too small (only where slices are subnormal: they
+//                       are rounded coarser than the projection) or not zero;
+//   f64_replay_kernel   returns at once when the marks decide every level (the
+//                       largest residual has the speculated exponent, or the
+//                       level and all after it are zero).  Otherwise
 //                       it reduces the recorded maxima, takes the true exponent
 //                       of the first wrong level (exact: every earlier level
 //                       was computed with verified exponents), re-speculates
@@ -145,6 +147,12 @@ __device__ inline int ceil_log2_pos(double m) {
 __device__ inline unsigned long long dbits(double x) {
     return (unsigned long long)__double_as_longlong(x);
 }
+
+// Marks of the split pass in F64SplitState::seen, bit r of each for level r: some
+// block's maximum has the speculated exponent, a larger one, or is not zero.
+__device__ inline unsigned seen_hit(unsigned long long levels) { return (unsigned)levels; }
+__device__ inline unsigned seen_above(unsigned long long levels) { return (unsigned)levels << 8; }
+__device__ inline unsigned seen_nonzero(unsigned long long levels) { return (unsigned)levels << 16; }
 
 // Operands of one launch and the split of its grid between them.
 struct F64SplitArgs {
@@ -478,7 +486,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) void split_f64_kernel(F64SplitArgs a
     // lane r of wave 0 holds the block's maximum of level r
     if (threadIdx.x >= 64) return;
     const int r = threadIdx.x;
-    bool hit = false;
+    bool hit = false, above = false, nonzero = false;
     if (r >= 1 && r < NLEV) {
         double m = red[r][0];
         for (int i = 1; i < SPLIT_THREADS / 64; ++i) m = fmax(m, red[r][i]);
@@ -486,11 +494,14 @@ __global__ __launch_bounds__(SPLIT_THREADS) void split_f64_kernel(F64SplitArgs a
         int vr = v[1];
 #pragma unroll
         for (int t = 2; t < 6; ++t) vr = r == t ? v[t] : vr;
-        hit = m > 0.0 && ceil_log2_pos(m) == vr;
+        nonzero = m > 0.0;
+        above = m > ldexp(1.0, vr);
+        hit = nonzero && !above && ceil_log2_pos(m) == vr;
     }
-    const unsigned mask = (unsigned)__ballot(hit);
+    const unsigned mask = seen_hit(__ballot(hit)) | seen_above(__ballot(above)) |
+                          seen_nonzero(__ballot(nonzero));
     if (threadIdx.x == 0 && mask) {
-        // once a level is confirmed the later blocks skip the atomic
+        // once a level is marked the later blocks skip the atomic
         const unsigned old = __hip_atomic_load(&op.st->seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (mask & ~old) atomicOr(&op.st->seen, mask);
     }
@@ -577,10 +588,19 @@ __device__ inline void first_verification(const F64SplitArgs &a, int o, int nlev
     int v[6];
 #pragma unroll
     for (int r = 0; r < 6; ++r) v[r] = op.st->v[r];
-    const unsigned want = v[0] == V_ZERO ? 0u : ((1u << nlev) - 2u);
+    // The marks confirm the chain when every level before the first identically
+    // zero one was hit and none exceeded (the same for all threads)
+    const unsigned levels = (1u << nlev) - 2u, seen = op.st->seen;
+    const unsigned zero = levels & ~(seen >> 16);   // (seen_nonzero)
+    const unsigned before = zero ? levels & ((zero & (0u - zero)) - 1u) : levels;
     unsigned long long mb[6] = {0, 0, 0, 0, 0, 0};
-    const bool confirmed = (op.st->seen & want) == want;   // the same for all threads
-    if (!confirmed) {
+    const bool confirmed =
+        v[0] == V_ZERO || ((seen & seen_above(levels)) == 0u && (seen & before) == before);
+    if (confirmed) {
+#pragma unroll
+        for (int r = 1; r < 6; ++r)
+            if (zero != 0u && (1u << r) > before) v[r] = V_ZERO;
+    } else {
         double mx[6];
 #pragma unroll
         for (int r = 1; r < 6; ++r) {

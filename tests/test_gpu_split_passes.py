@@ -75,3 +75,41 @@ def test_dgemm_with_replays_bit_exact(emu, M, N, K, ra, rb, nprod):
         got = np.ascontiguousarray(C[r, c])
         assert np.array_equal(got.view(np.uint64), ref.view(np.uint64))
     assert emu.domain_status() == st
+
+
+def test_subnormal_slices_exceed_the_chain(emu):
+    """Near the lower end of the domain the slices are subnormal and rounded
+    coarser than the projection, so a residual can be larger than the chain
+    speculated.  One k-block's work item shows such a residual (2^-134 at level
+    2), others have exactly the speculated maximum of one level each."""
+    X = np.zeros((64, 192))
+    X[:2, 0] = [2.0 ** -121 + 2.0 ** -138, 2.0 ** -120]
+    X[0, 32] = 2.0 ** -121 + 1.5 * 2.0 ** -130
+    X[0, 64] = 2.0 ** -121 + 2.0 ** -134
+    X[0, 96] = 2.0 ** -121 + 2.0 ** -147
+    X[0, 128] = 2.0 ** -121 + 2.0 ** -156
+    X[0, 160] = 2.0 ** -121 + 2.0 ** -165
+    ref, v, _, st = O.split_f64(X)
+    assert list(v[:3]) == [-120, -129, -134] and st == O.ST_SUBNORMAL
+    for as_b in (0, 1):
+        emu.domain_status()
+        s, vg = emu.split_f64(torch.from_numpy(X.T.copy() if as_b else X).cuda(), as_b=bool(as_b))
+        s = s.cpu().numpy().view(np.uint16)
+        assert np.array_equal(vg.cpu().numpy(), v)
+        assert np.array_equal(s.transpose(0, 2, 1) if as_b else s, ref)
+        assert emu.domain_status() == st
+
+
+@pytest.mark.parametrize("zero_from", [1, 2, 4])
+def test_identically_zero_levels(emu, zero_from):
+    """Integers of 8 zero_from bits leave nothing for the levels after those."""
+    n = 8 * zero_from
+    rng = np.random.default_rng(n)
+    X = rng.integers(-2 ** n, 2 ** n, (130, 1101)).astype(np.float64)
+    X[5, 7] = 2.0 ** n
+    ref, v, _, st = O.split_f64(X)
+    s, vg = emu.split_f64(torch.from_numpy(X).cuda())
+    zero = np.iinfo(np.int32).min
+    assert v[zero_from - 1] > zero and (v[zero_from:] == zero).all()
+    assert np.array_equal(vg.cpu().numpy(), v)
+    assert np.array_equal(s.cpu().numpy().view(np.uint16), ref)
