@@ -21,7 +21,7 @@ __device__ inline unsigned block_or(unsigned v) {
     return v;
 }
 
-// Decode the block's (k-block, row-group) pair and the thread's row/chunk.
+// Decode a (k-block, row-group) pair of SPLIT_THREADS threads and the thread's row/chunk.
 struct ItemCoords {
     int64_t kb, prow;
     int q;
@@ -31,7 +31,7 @@ __device__ inline ItemCoords item_coords(int64_t pair, int RG) {
     ItemCoords c;
     c.kb = pair / RG;
     int64_t rg = pair - c.kb * RG;
-    c.prow = rg * ROWS_PER_BLOCK + (threadIdx.x >> 2);
+    c.prow = rg * ROWS_PER_BLOCK + (threadIdx.x % SPLIT_THREADS >> 2);
     c.q = threadIdx.x & 3;
     return c;
 }
@@ -134,6 +134,8 @@ __global__ __launch_bounds__(SPLIT_THREADS) void split_f32_kernel(F32SplitArgs a
 constexpr int MAX_THREADS = 512;      // threads and blocks per operand of the maximum
 constexpr int MAX_BLOCKS = 256;
 constexpr int SPLIT_BLOCKS = 1024;    // blocks per operand of the split pass
+constexpr int REPLAY_THREADS = 512;   // threads of a replay block: ITEMS items at a time
+constexpr int REPLAY_ITEMS = REPLAY_THREADS / SPLIT_THREADS;
 // the row skew of one k-block holds a partial per block (tiles have >= 64 rows)
 static_assert(ROW_SKEW_TILES * ROW_GROUP * KBLK * 2 >= SPLIT_BLOCKS * 8 && SPLIT_BLOCKS >= MAX_BLOCKS,
               "partial maxima");
@@ -420,9 +422,10 @@ __device__ __forceinline__ void split_f64_plain(const F64SplitOperand &op, int64
     if (nonfinite) st |= ST_OVERFLOW;
 }
 
-// Block maxima of the levels in red[r][0 .. 3] (one per wave), after a barrier.
+// Block maxima of the levels in red[r][0 .. W - 1] (one per wave), after a barrier.
+template <int W>
 __device__ inline void block_level_max(const double (&mx)[6], int r0, int nlev,
-                                       double (&red)[6][SPLIT_THREADS / 64]) {
+                                       double (&red)[6][W]) {
     const int w = threadIdx.x >> 6;
 #pragma unroll
     for (int r = 1; r < 6; ++r) {
@@ -583,7 +586,7 @@ __device__ inline void publish_chains(const F64SplitArgs &a, const Chains &c) {
 // level was mis-speculated, and the first level to recompute.  Called by the
 // whole block; red is block scratch.
 __device__ inline void first_verification(const F64SplitArgs &a, int o, int nlev, Chains &c,
-                                          double (&red)[6][SPLIT_THREADS / 64]) {
+                                          double (&red)[6][REPLAY_THREADS / 64]) {
     const F64SplitOperand &op = o ? a.op[1] : a.op[0];
     int v[6];
 #pragma unroll
@@ -607,7 +610,7 @@ __device__ inline void first_verification(const F64SplitArgs &a, int o, int nlev
             mx[r] = 0.0;
             if (r >= nlev) continue;
             const double *part = partial_max(op, a.KB, r);
-            for (int i = threadIdx.x; i < (o ? a.blocks1 : a.blocks0); i += SPLIT_THREADS)
+            for (int i = threadIdx.x; i < (o ? a.blocks1 : a.blocks0); i += REPLAY_THREADS)
                 mx[r] = fmax(mx[r], part[i]);
         }
         __syncthreads();   // red may still be read by an earlier use
@@ -616,7 +619,7 @@ __device__ inline void first_verification(const F64SplitArgs &a, int o, int nlev
         for (int r = 1; r < 6; ++r) {
             if (r >= nlev) continue;
             double m = red[r][0];
-            for (int i = 1; i < SPLIT_THREADS / 64; ++i) m = fmax(m, red[r][i]);
+            for (int i = 1; i < REPLAY_THREADS / 64; ++i) m = fmax(m, red[r][i]);
             mb[r] = dbits(m);
         }
     }
@@ -657,8 +660,8 @@ __device__ inline void replay_chain(const F64SplitArgs &a, int o, int pass, int 
 // has as many units as the launch has blocks, so nobody waits for a unit that
 // was not drawn.  (One unit per block and pass: with two, the draws alone took
 // 40 us a pass.)
-__global__ __launch_bounds__(SPLIT_THREADS, 4) void f64_replay_kernel(F64SplitArgs a, int nlev) {
-    __shared__ double red[6][SPLIT_THREADS / 64];
+__global__ __launch_bounds__(REPLAY_THREADS, 4) void f64_replay_kernel(F64SplitArgs a, int nlev) {
+    __shared__ double red[6][REPLAY_THREADS / 64];
     __shared__ unsigned drawn;
     __shared__ Chains c;
     first_verification(a, 0, nlev, c, red);
@@ -712,15 +715,16 @@ __global__ __launch_bounds__(SPLIT_THREADS, 4) void f64_replay_kernel(F64SplitAr
         if (r0 >= 0) {
             double mx[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
             unsigned st = 0;
-            if (op.as_b) split_f64_pass<true, true>(op, a.KB, b, nb, v, r0, nlev, cst, false, mx, st);
-            else split_f64_pass<false, true>(op, a.KB, b, nb, v, r0, nlev, cst, false, mx, st);
+            const int ib = b * REPLAY_ITEMS + (int)(threadIdx.x / SPLIT_THREADS), nib = nb * REPLAY_ITEMS;
+            if (op.as_b) split_f64_pass<true, true>(op, a.KB, ib, nib, v, r0, nlev, cst, false, mx, st);
+            else split_f64_pass<false, true>(op, a.KB, ib, nib, v, r0, nlev, cst, false, mx, st);
             st = block_or(st);
             if ((threadIdx.x & 63) == 0 && st) atomicOr(a.status, st);
             block_level_max(mx, r0, nlev, red);
             const int r = threadIdx.x;
             if (r > r0 && r >= 1 && r < nlev) {
                 double m = red[r][0];
-                for (int i = 1; i < SPLIT_THREADS / 64; ++i) m = fmax(m, red[r][i]);
+                for (int i = 1; i < REPLAY_THREADS / 64; ++i) m = fmax(m, red[r][i]);
                 // most units find a maximum that is already as large
                 if (dbits(m) > __hip_atomic_load(&out->maxbits[r], __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
@@ -1130,18 +1134,21 @@ hipError_t launch_split_f64(const F64SplitOperand *ops, int nops, int64_t KB, in
         case 5: split_f64_kernel<5><<<g, SPLIT_THREADS, 0, s>>>(a); break;
         default: split_f64_kernel<6><<<g, SPLIT_THREADS, 0, s>>>(a); break;
     }
-    // One replay unit per two items, at most 512 (1024 for large operands: four
-    // blocks per CU), shared between the operands by their items.  Drawing and
-    // counting cost about 30 ns a unit and pass (d = 6 at 2048^3, every level
-    // replayed, split phase: 289 us with 512 units, 415 with 1024; 260 with
-    // the separate launches of before, which took 20 us more whenever nothing
-    // is replayed), and a launch that finds nothing to do costs less the
-    // fewer blocks it has (2.2 us for 320, 4.7 for 2048).
+    // A replay unit per two items (the block's two halves), at most 256 (512 for
+    // large operands: two blocks per CU), shared between the operands by their
+    // items.  Drawing and counting cost about 30 ns a unit and pass: d = 6 at
+    // 2048^3, every level replayed, split phase, us: 250 with 256 units of 512
+    // threads, 329 with 512 of 256, 355 with 128 of 1024, 288 with the separate
+    // launches of before, which took 20 us more whenever nothing is replayed; at
+    // 256^3 69, 78, 123 and 74 (84 with four items a unit).  A launch that finds
+    // nothing to do costs less the fewer blocks it has (2.2 us for 320, 4.7 for
+    // 2048).
     const int64_t items0 = KB * (ops[0].Rlive / ROWS_PER_BLOCK);
     const int64_t items = items0 + (nops > 1 ? KB * (ops[1].Rlive / ROWS_PER_BLOCK) : 0);
-    const int most = clamp(items / 2, items < 16384 ? 512 : 1024), gr = most < nops ? nops : most;
+    const int most = clamp(items / REPLAY_ITEMS, (items < 16384 ? 512 : 1024) / REPLAY_ITEMS);
+    const int gr = most < nops ? nops : most;
     a.units0 = nops == 1 ? gr : clamp(gr * items0 / items, gr - 1);
-    f64_replay_kernel<<<gr, SPLIT_THREADS, 0, s>>>(a, nlev);
+    f64_replay_kernel<<<gr, REPLAY_THREADS, 0, s>>>(a, nlev);
     return hipGetLastError();
 }
 
