@@ -54,9 +54,10 @@ _CSRC = "paper_2609_04663_amd/csrc/"
 # sources a GEMM kernel is compiled from (a stored traffic figure is only used
 # while their hash is unchanged)
 KERNEL_SOURCES = {
-    "sgemm": [_CSRC + "gemm_f32.hip", _CSRC + "gemm_common.h", _CSRC + "emu_internal.h"],
+    "sgemm": [_CSRC + "gemm_f32.hip", _CSRC + "gemm_common.h", _CSRC + "emu_internal.h",
+              _CSRC + "dgemm_plan.h"],
     "dgemm": [_CSRC + "gemm_f64.hip", _CSRC + "gemm_f64.h", _CSRC + "gemm_f64t.hip",
-              _CSRC + "gemm_common.h", _CSRC + "emu_internal.h"],
+              _CSRC + "gemm_common.h", _CSRC + "emu_internal.h", _CSRC + "dgemm_plan.h"],
 }
 
 

@@ -1,8 +1,9 @@
 // Host side of the C ABI declared in include/emu.h: argument validation,
 // the device workspace, launch sequencing on the current stream, status and
 // error reporting.  Every entry point validates its arguments before any HIP
-// call; no entry point synchronises the host except emu_domain_status and
-// emu_release_workspace.
+// call.  The host is synchronised by emu_domain_status, emu_release_workspace,
+// emu_profile_read, emu_profile_enable(0), a call that grows the workspace, and
+// the K-binned scope (once per call, to size its groups).
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -456,7 +457,6 @@ int emu_sgemm(int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, cons
 
 namespace {
 
-// Bytes of workspace (after the header) an emulated DGEMM of depth d needs.
 // How one emulated DGEMM runs: with the row/column weights of the scale-aware
 // split, and with the native FP64 fallback armed.
 struct DgemmOpts {

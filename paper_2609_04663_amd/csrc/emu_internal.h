@@ -211,14 +211,12 @@ hipError_t launch_kbin_classes(const double *A, int64_t lda, bool ta, const doub
 hipError_t launch_axpby_f64(const double *P, int64_t ldp, double *C, int64_t ldc, int64_t M,
                             int64_t N, double alpha, double beta, const unsigned *skip_if,
                             hipStream_t s);
-// alpha, beta: C = alpha P + beta C (see out_update); 1, 0 stores P
-// Split-K factor of the emulated SGEMM: 1 unless the output tiles fill at most
-// half of the chip, else up to 16 (64-row tiles: 64) splits of whole reduction panels.  splits > 1 needs part:
-// splits x M x N floats of scratch for the partial sums.
 // CUs of the current device (256 on MI355X), read once per process.
 int device_cu_count();
 int sgemm_tile_m(int64_t M, int64_t N, int64_t KB);   // 192, 128 or 64 output rows per tile
 int sgemm_tile_n(int tile_m);                          // its columns: 128, 128 or 64
+// Split-K factor of the emulated SGEMM: 1 unless the output tiles fill at most
+// half of the chip, else up to 16 (64-row tiles: 64) splits of whole reduction panels.
 int sgemm_splits(int64_t M, int64_t N, int64_t KB, int tile_m);
 // The streamed-split SGEMM: op(A) op(B) read in FP32 by the GEMM, split per
 // k-block in the workgroup (128 x 128 tiles); same result bits as the split
@@ -227,6 +225,8 @@ hipError_t launch_gemm_f32_streamed(const float *A, int64_t lda, bool ta, const 
                                     int64_t ldb, bool tb, float *C, int64_t M, int64_t N,
                                     int64_t K, int64_t ldc, float alpha, float beta, int splits,
                                     float *part, unsigned *status, hipStream_t s);
+// C = alpha P + beta C (see out_update; 1, 0 stores P); splits > 1 needs part:
+// splits x M x N floats of scratch for the partial sums.
 hipError_t launch_gemm_f32(const uint16_t *Ap, const uint16_t *Bp, float *C, int64_t M, int64_t N,
                            int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc, float alpha,
                            float beta, int tile_m, int splits, float *part, hipStream_t s);

@@ -45,8 +45,9 @@ inline int persistent_workgroups() { return persistent_workgroups(device_cu_coun
 template <int D, int BM, int NS, bool ACC64_LDS>
 hipError_t launch_s(const DgemmArgs &a, hipStream_t s);
 // gemm_f64w.hip: 16 x 16 x 32 MFMA, output tile (32 BMW) x 64.  PERSIST_OK =
-// false: the caller only launches long reductions here, which never take the
-// persistent grid (its instantiation is then not built).
+// false: the caller only launches long reductions, or grids of at most one tile
+// per CU, which do not take the persistent grid (its instantiation is then not
+// built; more tiles would run one per workgroup).
 template <int D, int NS, bool ACC64_LDS, int BMW = 1, bool PERSIST_OK = true>
 hipError_t launch_w(const DgemmArgs &a, hipStream_t s);
 // gemm_f64t.hip: 32 x 32 x 16 MFMA over whole panels, output tile (64 t_bm(D)) x 64

@@ -15,10 +15,11 @@
 // Three kernels.  gemm_f64_kernel (gemm_f64s.hip): 32 x 32 x 16 MFMA, 4 waves in a 2 x 2
 // grid; wave tile (32 BM) x 32, output tile (64 BM) x 64.  gemm_f64w_kernel
 // (gemm_f64w.hip): 16 x 16 x 32 MFMA on a (16 BMW) x 32 wave tile, one barrier
-// per k-block; it runs depths d >= 7 and small grids.  gemm_f64t_kernel
-// (gemm_f64t.hip): 32 x 32 x 16 MFMA over whole panels, d = 3 .. 6 on grids that
-// fill the CUs.  (The choice is made in launch_gemm_f64.)  Per k-block of 32 the d planes of both operands are copied
-// straight into LDS (global_load_lds_dwordx4) through a ring of LDS stages.
+// per k-block; it runs depths d >= 7, small grids and d = 6 where the panels do
+// not suit.  gemm_f64t_kernel (gemm_f64t.hip): 32 x 32 x 16 MFMA over whole
+// panels, d = 3 .. 6 on grids that fill the CUs (panel_kernel_wanted in
+// dgemm_plan.h; the choice among the others is made in launch_gemm_f64).  Per
+// k-block of 32 the d planes of both operands are copied straight into LDS (global_load_lds_dwordx4) through a ring of LDS stages.
 // Each wave keeps one FP32 accumulator set per product for the whole panel
 // (all N_p live, so every fragment read from LDS feeds every product that
 // uses it) and an FP64 accumulator tile.
@@ -30,13 +31,18 @@ hipError_t launch_gemm_f64(const uint16_t *Ap, const uint16_t *Bp, double *C, in
                            int64_t N, int64_t KB, int64_t RpadA, int64_t RpadB, int64_t ldc,
                            const int *sa, const int *sb, double alpha, double beta, int d,
                            bool panels, const unsigned *skip_if, hipStream_t s) {
-    // First gemm_f64t_kernel where the plan packed the operands for it.  The other calls of depths
-    // 1 .. 5 take the wide kernel's 64 x 64 tiles (BMW = 2) where it measured
-    // faster than the 32 x 32 x 16 kernel: long reductions (K > 1024) of d = 2,
-    // 4 and 5 (8, 2 and 5 % at 8192^3), and grids of d = 1 .. 3 whose 128- or
+    // First gemm_f64t_kernel where the plan packed the operands for it.  The
+    // other calls of depths 1 .. 5 take the wide kernel's 64 x 64 tiles (BMW = 2)
+    // where it measured faster than the 32 x 32 x 16 kernel: long reductions
+    // (K > 1024) of d = 2 (8 % at 8192^3), and grids of d = 1 .. 3 whose 128- or
     // 256-row tiles would number fewer than the CUs (1.5 - 1.9x at 1000 x 1000
-    // x 8200).  The other long reductions of d = 1 take its 128 x 64 tiles (BMW
-    // = 4; 7-40 % faster).  All kernels give the same bits.
+    // x 8200).  Long reductions of d = 4 and 5 come here only with fewer tiles
+    // than CUs, where both kernels take the same time within 5 % (32 x 32 x 16 /
+    // wide, us: d = 4 1024 x 1024 x 4096 87.2 / 88.7, 1024 x 768 x 8192 141.8 /
+    // 149.1, 1400 x 1400 x 8200 326.3 / 326.7; d = 5 900 x 900 x 4096 118.9 /
+    // 115.8, 1000 x 1000 x 16384 450.5 / 448.6).  The
+    // other long reductions of d = 1 take its 128 x 64 tiles (BMW = 4; 7-40 %
+    // faster).  All kernels give the same bits.
     const DgemmArgs a = {Ap, Bp, C, M, N, KB, RpadA, RpadB, ldc, sa, sb, alpha, beta,
                          skip_if};
     const int pw = persistent_workgroups();

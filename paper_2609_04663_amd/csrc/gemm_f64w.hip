@@ -6,8 +6,9 @@
 // per product.  Workgroup: 4 waves in a 2 x 2 grid, output tile 32 x 64; one
 // k-block of 32 reduction indices (one MFMA depth) per trip and one barrier
 // per trip, with the copies and fragment reads spread over the trip's MFMAs
-// and copies issued two trips ahead.  d = 6 runs here too: measured at
-// M = N = K = 8192 it is about 5 % faster than on the 32 x 32 kernel.
+// and copies issued two trips ahead.  d = 6 runs here too where the
+// panel kernel (gemm_f64t.hip) does not suit: small grids, reductions that pad
+// badly to whole panels or need fewer rounds of these smaller tiles.
 // Depths d <= 5 (d planes per operand) can take a 32 x 32 wave tile here
 // (BMW = 2: 2 x 2 blocks, 16 registers per product, output tile 64 x 64) or,
 // with few products, 64 x 32 (BMW = 4, output tile 128 x 64).
