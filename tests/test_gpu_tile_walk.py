@@ -54,8 +54,27 @@ def test_walked_tiles_bit_exact(emu, nprod, K):
     assert torch.isnan(C[:, N:]).all() and not np.isnan(got).any()
 
 
+# 450 tiles of 128 x 64, 900 of 64 x 64: the panel kernel at every depth, d = 4 too
+# (above, its short reductions take fewer rounds on the other kernel); K = 480
+# pads to 512
+PANELS = (2300, 1540)
+
+
+@pytest.mark.parametrize("K", [256, 480, 512, 1024])
+@pytest.mark.parametrize("nprod", [10, 21])
+def test_walked_tiles_by_rounds(emu, nprod, K):
+    M, N = PANELS
+    A = S.make("wide", K + nprod, (M, K), np.float64)
+    B = S.make("uniform", K + nprod + 1, (K, N), np.float64)
+    r, c = sample(M, N, K)
+    ref, st = O.emu_dgemm_entries(A, B, r, c, nprod)
+    got = emu.dgemm(dev(A), dev(B), nprod).cpu().numpy()
+    assert st == 0 and same_bits(got[r, c], ref)
+
+
 # one product count per kernel: 1, 3 (128- and 64-row tiles), 6 .. 21, 26 and up
-@pytest.mark.parametrize("M,N,K", [(1024, 1152, 256), (1000, 1100, 300), (300, 70, 300)])
+@pytest.mark.parametrize("M,N,K", [(1024, 1152, 256), (1000, 1100, 300), (300, 70, 300),
+                                   (*PANELS, 256)])
 @pytest.mark.parametrize("nprod", [1, 3, 6, 10, 15, 21, 36])
 def test_store_paths_bit_exact(emu, nprod, M, N, K):
     A = S.make("normal", 3 * nprod, (M, K), np.float64)
