@@ -573,25 +573,34 @@ __global__ __launch_bounds__(256, 1) void gemm_f32s_kernel(
         M, N, dst, whole ? ldc : N, whole ? alpha : 1.0f, whole ? beta : 0.0f, nullptr, nullptr);
 }
 
-// Split-K combination: C = alpha (sum of the splits' partial sums, in split
-// order, FP32) + beta C, with the output update of the single-pass kernel.
+// Split-K combination: C = alpha (sum of the splits' partial sums, FP32) + beta C,
+// with the output update of the single-pass kernel.  Up to 16 splits are added in
+// split order; more are added in groups of eight first (one chain of 57 made
+// 119 x 69 x 14422 30 % less accurate, 1.64e-7 against 1.25e-7 with 16 splits).
 __global__ void reduce_splits_kernel(const float *__restrict__ part, int splits, int64_t M,
                                      int64_t N, float *__restrict__ C, int64_t ldc, float alpha,
                                      float beta) {
     const int64_t total = M * N;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
          i += (int64_t)gridDim.x * blockDim.x) {
-        float p = part[i];
-        // eight loads in flight; the sums stay in split order
-        int sp = 1;
+        // eight loads in flight
+        const bool groups = splits > 16;
+        float p = groups ? 0.0f : part[i];
+        int sp = groups ? 0 : 1;
         for (; sp + 8 <= splits; sp += 8) {
             float x[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) x[u] = part[(sp + u) * total + i];
+            float q = groups ? x[0] : p + x[0];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) p += x[u];
+            for (int u = 1; u < 8; ++u) q += x[u];
+            p = groups ? p + q : q;
         }
-        for (; sp < splits; ++sp) p += part[sp * total + i];
+        if (sp < splits) {
+            float q = groups ? 0.0f : p;
+            for (; sp < splits; ++sp) q += part[sp * total + i];
+            p = groups ? p + q : q;
+        }
         const int64_t row = i / N, col = i - row * N;
         C[row * ldc + col] =
             out_update(p, alpha, beta, beta != 0.0f ? C[row * ldc + col] : 0.0f);
